@@ -243,17 +243,28 @@ def work(case):
 
 
 # ---------------------------------------------------------------- 64-bit reference
+def _split(v):
+    """A long double array as head (26 bits, so that products of two heads are
+    exact) and rest, in FP64 on the GPU."""
+    f = v.astype(np.float64) * 134217729.0  # 2^27 + 1
+    head = f - (f - v.astype(np.float64))
+    return torch.from_numpy(head).cuda(), torch.from_numpy((v - head).astype(np.float64)).cuda()
+
+
 def _legendre_blocks(theta, lmax, mmax, values):
     """Blocks of normalised lambda_lm(cos theta) for m >= 0: yields (m0, l0,
     lam[l, m, ring]) over all l >= m0 (zero for l < m), at most `values` values
-    at a time.  The recurrence of Sec. 2.2 with an exponent per (m, ring)."""
-    x = torch.from_numpy(np.cos(theta)).cuda()[None, :]
-    s = np.sin(theta).astype(np.longdouble)[None, :]
+    at a time.  The recurrence of Sec. 2.2 with an exponent per (m, ring); the
+    coefficients and cos theta are carried to more than FP64 (head and rest),
+    since their rounding would add up along l more than that of the values."""
+    th = theta.astype(np.longdouble)
+    xh, xr = (v[None, :] for v in _split(np.cos(th)))
+    s = np.sin(th)[None, :]
     mu = np.empty(mmax + 1, dtype=np.longdouble)
     mu[0] = 1 / np.sqrt(4 * _PI_L)
     for m in range(1, mmax + 1):
         mu[m] = -mu[m - 1] * np.sqrt(np.longdouble(2 * m + 1) / (2 * m))
-    nm = max(1, min(mmax + 1, 1 << 20) if theta.size * (mmax + 1) <= 1 << 19 else (1 << 19) // theta.size)
+    nm = max(1, min(mmax + 1, (1 << 19) // theta.size))
     for m0 in range(0, mmax + 1, nm):
         ms = np.arange(m0, min(mmax + 1, m0 + nm))
         man, ex = np.frexp(mu[ms][:, None] * s ** ms[:, None].astype(np.longdouble))
@@ -262,22 +273,22 @@ def _legendre_blocks(theta, lmax, mmax, values):
         carrier[man == 0] = 0.0
         seed, sc = torch.from_numpy(carrier).cuda(), torch.from_numpy(sc).cuda()
         p1, p2 = torch.zeros_like(seed), torch.zeros_like(seed)
-        ls = np.arange(m0, lmax + 1, dtype=np.float64)[:, None]
-        mm = ms.astype(np.float64)[None, :]
+        ls = np.arange(m0, lmax + 1, dtype=np.longdouble)[:, None]
+        mm = ms.astype(np.longdouble)[None, :]
         with np.errstate(all="ignore"):
-            beta = np.sqrt((4 * ls * ls - 1) / (ls * ls - mm * mm))
-            prev = np.sqrt((4 * (ls - 1) ** 2 - 1) / ((ls - 1) ** 2 - mm * mm))
-            ratio = np.where(ls > mm + 1, beta / prev, 0.0)
-        beta = torch.from_numpy(np.where(ls > mm, beta, 0.0)).cuda()[:, :, None]
-        ratio = torch.from_numpy(ratio).cuda()[:, :, None]
+            beta = np.where(ls > mm, np.sqrt((4 * ls * ls - 1) / (ls * ls - mm * mm)), 0)
+            ratio = np.where(ls > mm + 1, beta / np.sqrt((4 * (ls - 1) ** 2 - 1) / ((ls - 1) ** 2 - mm * mm)), 0)
+        (bh, br), (rh, rr) = ((h[:, :, None], r[:, :, None]) for h, r in (_split(beta), _split(ratio)))
         nl = max(1, values // (len(ms) * theta.size))
         for l0 in range(m0, lmax + 1, nl):
             lam = torch.empty((min(nl, lmax + 1 - l0), len(ms), theta.size), dtype=torch.float64, device="cuda")
             for i in range(lam.shape[0]):
-                l = l0 + i
-                p = beta[l - m0] * x * p1 - ratio[l - m0] * p2
-                if l - m0 < len(ms):
-                    p[l - m0] = seed[l - m0]
+                k = l0 + i - m0
+                # beta x p1 - ratio p2, the exact product of the heads first
+                e = (bh[k] * xr).addcmul_(br[k], xh).addcmul_(br[k], xr).mul_(p1).addcmul_(rr[k], p2, value=-1)
+                p = e.addcmul_(bh[k] * xh, p1).addcmul_(rh[k], p2, value=-1)
+                if k < len(ms):
+                    p[k] = seed[k]
                 p1, p2 = p, p1
                 if i % 16 == 15 or i == lam.shape[0] - 1:
                     big = (sc < 0) & (p1.abs() > 2.0 ** -60)
@@ -286,8 +297,8 @@ def _legendre_blocks(theta, lmax, mmax, values):
             yield m0, l0, lam
 
 
-def _columns(alm, lmax, m0, nm, l0, nl):
-    """The slice a[l, m, map] of packed a_lm (zero for l < m), and the packed positions."""
+def _columns(lmax, m0, nm, l0, nl):
+    """Packed positions of the block a[l, m], and where l >= m."""
     l = torch.arange(l0, l0 + nl, device="cuda")[:, None]
     m = torch.arange(m0, m0 + nm, device="cuda")[None, :]
     at = (m * (2 * lmax + 1 - m) // 2 + l).clamp(min=0)
@@ -332,7 +343,7 @@ def _exact_one(c, x):
     own = torch.arange(north, device="cuda") == south  # the equator ring counts once
     for m0, l0, lam in _legendre_blocks(g.theta[:north], lmax, mmax, 1 << 26):
         nl, nm = lam.shape[0], lam.shape[1]
-        at, ok = _columns(None, lmax, m0, nm, l0, nl)
+        at, ok = _columns(lmax, m0, nm, l0, nl)
         for par in (0, 1):
             # l - m of this parity: the southern ring takes (-1)^(l+m) of the northern value
             sel = ok & ((torch.arange(l0, l0 + nl, device="cuda")[:, None]
