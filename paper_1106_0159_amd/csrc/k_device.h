@@ -35,16 +35,25 @@ inline int64_t padded_m(int mmax) {
 inline bool grid_ok(int64_t n) { return n > 0 && n < (int64_t)INT32_MAX; }
 
 // Wave-wide min / max, returned as a wave-uniform (scalar) value so that
-// loops bounded by it stay uniform and their coefficient loads scalar.
+// loops bounded by it stay uniform and their coefficient loads scalar.  Lane
+// exchanges in registers (DPP within a row of 16, then the permlane swaps):
+// six dependent LDS permutes instead would add about 0.2 us to every kernel's start.
+template <class Op>
+__device__ __forceinline__ int wave_reduce(int v, Op op) {
+    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, false));   // quad_perm [1,0,3,2]
+    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, false));   // quad_perm [2,3,0,1]
+    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, false));  // row_half_mirror
+    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x140, 0xf, 0xf, false));  // row_mirror
+    const auto r16 = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+    v = op((int)r16[0], (int)r16[1]);
+    const auto r32 = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+    return __builtin_amdgcn_readfirstlane(op((int)r32[0], (int)r32[1]));
+}
 __device__ __forceinline__ int wave_min(int v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v = min(v, __shfl_xor(v, off));
-    return __builtin_amdgcn_readfirstlane(v);
+    return wave_reduce(v, [](int a, int b) { return min(a, b); });
 }
 __device__ __forceinline__ int wave_max(int v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v = max(v, __shfl_xor(v, off));
-    return __builtin_amdgcn_readfirstlane(v);
+    return wave_reduce(v, [](int a, int b) { return max(a, b); });
 }
 
 // Read-only coefficient data (recurrence coefficients, scaled a_lm) seen

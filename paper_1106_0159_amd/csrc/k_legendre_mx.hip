@@ -128,6 +128,35 @@ __global__ __launch_bounds__(kBlock) void k_prescale_mx(int lmax, int nmaps, int
     }
 }
 
+// Start of the one-step recurrence q_l (lambda_lm = c_lm q_l) of a slot, from
+// its tabulated start of the x^2 recurrence at l0 = m + 2 j0: with k = j0 - 1,
+// lambda_{l0-1} = x po_k q_k and lambda_{l0-2} = pe1_k q_k + pe2_{k-1} q_{k-1}
+// give (q_{l0-2}, q_{l0-1}); at j0 = 0 (-lambda_mm, 0) makes the first step
+// yield the seed.  ls = l0, or a value above lmax where the slot is not started.
+struct MxStart {
+    int ls;
+    double2 st;
+};
+__device__ __forceinline__ MxStart mx_start(int lmax, int m, int nslots, int slot, double x, ParityFac f,
+                                            const double *__restrict__ cfac, const int32_t *__restrict__ jstart,
+                                            const double2 *__restrict__ state) {
+    MxStart r{lmax + 1, make_double2(0.0, 0.0)};
+    if (slot >= nslots) return r;
+    const int j0 = jstart[(int64_t)m * nslots + slot];
+    if (j0 >= jcol_len(lmax, m)) return r;
+    const int64_t jb = jcol_base(lmax, m) + j0;
+    const double2 s = state[(int64_t)m * nslots + slot];
+    r.ls = m + 2 * j0;
+    if (j0 == 0) {
+        r.st.x = f.pe1[jb] * s.x;
+    } else {
+        const int64_t at = (int64_t)m * (2 * lmax + 1 - m) / 2 + r.ls;
+        r.st.y = x * f.po[jb - 1] * s.y / cfac[at - 1];
+        r.st.x = fma(f.pe1[jb - 1], s.y, f.pe2[jb - 2] * s.x) / cfac[at - 2];
+    }
+    return r;
+}
+
 // LDS q tiles of one workgroup: per wave, parity and lane row, the four
 // 4-k words of a block as FP32, or (SPLIT) as bf16 in three planes (8-byte
 // words; a row of 5 words keeps the row writes and the operand reads free of
@@ -144,8 +173,9 @@ __global__ __launch_bounds__(kBlock, 2) void k_leg_syn_mx(int lmax, int mmax, in
                                                         int nmaps, int64_t mxblocks,
                                                         const int64_t *__restrict__ mxofs,
                                                         const void *__restrict__ ap,
-                                                        const double *__restrict__ alpha,
-                                                        const int32_t *__restrict__ lstart,
+                                                        const double *__restrict__ alpha, ParityFac fac,
+                                                        const double *__restrict__ cfac,
+                                                        const int32_t *__restrict__ jstart,
                                                         const double2 *__restrict__ state,
                                                         const double *__restrict__ sx,
                                                         const int32_t *__restrict__ rn,
@@ -165,8 +195,9 @@ __global__ __launch_bounds__(kBlock, 2) void k_leg_syn_mx(int lmax, int mmax, in
     const int slot = tile * kBlock + (int)threadIdx.x;
     const bool act = slot < nslots;
     const double x = act ? sx[slot] : 0.0;
-    const int ls = act ? lstart[(int64_t)m * nslots + slot] : lmax + 1;
-    const double2 stv = act ? state[(int64_t)m * nslots + slot] : make_double2(0.0, 0.0);
+    const MxStart start = mx_start(lmax, m, nslots, slot, x, fac, cfac, jstart, state);
+    const int ls = start.ls;
+    const double2 stv = start.st;
     const int lo = wave_min(ls);
     const int hi = wave_max(ls <= lmax ? ls : m);
 
@@ -403,8 +434,8 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void k_leg_ana_mx(i
                                                               int nmaps, int64_t nalm, int groups,
                                                               const double2 *__restrict__ delta,
                                                               const double *__restrict__ alpha,
-                                                              const double *__restrict__ cfac,
-                                                              const int32_t *__restrict__ lstart,
+                                                              const double *__restrict__ cfac, ParityFac fac,
+                                                              const int32_t *__restrict__ jstart,
                                                               const double2 *__restrict__ state,
                                                               const double *__restrict__ sx,
                                                               const int32_t *__restrict__ rn,
@@ -441,8 +472,9 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void k_leg_ana_mx(i
         const int slot = tile0(t) + lane;
         const bool act = slot < nslots;
         x[t] = act ? sx[slot] : 0.0;
-        ls[t] = act ? lstart[(int64_t)m * nslots + slot] : lmax + 1;
-        stv[t] = act ? state[(int64_t)m * nslots + slot] : make_double2(0.0, 0.0);
+        const MxStart start = mx_start(lmax, m, nslots, slot, x[t], fac, cfac, jstart, state);
+        ls[t] = start.ls;
+        stv[t] = start.st;
         q1[t] = q2[t] = 0.0;
         tlo[t] = wave_min(ls[t]);
         thi[t] = wave_max(ls[t] <= lmax ? ls[t] : m);
@@ -593,7 +625,7 @@ int launch_syn_mx_t(const CoefTables &c, const GeomPlan &p, const StartTable &s,
     SHT_HIP(hipGetLastError());
     hipLaunchKernelGGL((k_leg_syn_mx<NCF, F64S, SPLIT>), dim3((unsigned)gx, (unsigned)ncg), dim3(kBlock), 0, st, c.lmax, c.mmax,
                        p.nslots, tiles, dl, nmaps, c.mxblocks, c.mxofs, static_cast<const void *>(aprime),
-                       c.alpha, s.lstart, s.state, p.slot_x, p.slot_north, p.slot_south,
+                       c.alpha, parity_fac(c), c.cfac, s.jstart, s.state, p.slot_x, p.slot_north, p.slot_south,
                        static_cast<double2 *>(delta));
     SHT_HIP(hipGetLastError());
     return SHT_OK;
@@ -610,7 +642,7 @@ int launch_ana_mx_t(const CoefTables &c, const GeomPlan &p, const StartTable &s,
     if (groups > 1 && !partials) return SHT_EWORKSPACE;
     hipLaunchKernelGGL(k_leg_ana_mx<WAVES>, dim3((unsigned)gx, (unsigned)ncg), dim3(64 * WAVES), 0, st, c.lmax,
                        c.mmax, p.nslots, dl, nmaps, c.nalm, groups, static_cast<const double2 *>(delta), c.alpha,
-                       c.cfac, s.lstart, s.state, p.slot_x, p.slot_north, p.slot_south, static_cast<double2 *>(alm),
+                       c.cfac, parity_fac(c), s.jstart, s.state, p.slot_x, p.slot_north, p.slot_south, static_cast<double2 *>(alm),
                        static_cast<double2 *>(partials));
     SHT_HIP(hipGetLastError());
     return groups > 1 ? launch_ana_combine(c, nmaps, groups, partials, alm, st) : SHT_OK;

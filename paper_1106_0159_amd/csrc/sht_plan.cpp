@@ -208,7 +208,7 @@ CoefTables::~CoefTables() { release_device(dev, *this, owned); }
 
 StartTable::~StartTable() {
     std::vector<void *> v;
-    if (lstart) v.push_back(lstart);
+    if (jstart) v.push_back(jstart);
     if (state) v.push_back(state);
     release_device(dev, *this, v);
 }
@@ -245,6 +245,71 @@ static void coef_column(int lmax, int m, double *alpha, double *cfac) {
     }
 }
 
+// The x^2 recurrence of one m (FP64 kernels).  eq. assLegRec, lambda_l =
+// beta_l x lambda_{l-1} - rho_l lambda_{l-2} with rho_l = beta_l / beta_{l-1},
+// applied twice steps by two in l; for r_j = lambda_k / x, k = m + 2j + 1,
+//   r_{j+1} = (beta_{k+2} beta_{k+1} x^2 - beta_{k+2} rho_{k+1} / beta_k - rho_{k+2}) r_j
+//             - (beta_{k+2} rho_{k+1} rho_k / beta_k) r_{j-1},
+// and the even degrees are lambda_{k-1} = (r_j + rho_k r_{j-1}) / beta_k.  With
+// r_j = C_j q_j, C_0 = C_1 = 1 and C_{j+1} = (the factor of r_{j-1}) C_{j-1},
+// the coefficient of q_{j-1} is -1; C_j is carried in long double, so that its
+// rounding stays out of the recurrence.
+//
+// ra, rb (slots away from the poles) take beta and rho in long double.  rbp (the
+// GeomPlan::npolar slots next to the poles) takes them rounded to double, as a
+// direct evaluation of eq. betaDef has them: with colatitudes that close to the
+// pole rounded to double as well (build_slots), both roundings move a ring of a few
+// pixels by about 1e-12, and the FP64 path moves it as eq. assLegRec in double does.
+static void x2_column(int lmax, int m, double *ra, double *rb, double *rbp, double *pe1, double *pe2, double *po) {
+    const int n = jcol_len(lmax, m);
+    ra[0] = rb[0] = rbp[0] = 0.0;
+    {
+        auto beta = [m](int l) {
+            const long double L = l, M = m;
+            return sqrtl((4.0L * L * L - 1.0L) / (L * L - M * M));
+        };
+        // with rho = beta / beta' the factors reduce to h_j = 1 / (beta_{k+1}
+        // beta_{k+2}): A_j = C_{j-1} / (C_j h), factor of r_{j-1} = h_{j-1} / h_j
+        long double c0 = 1.0L, c1 = 1.0L, h0 = 0.0L, b0 = beta(m + 1);  // C_{j-1}, C_j, h_{j-1}, beta_k
+        for (int j = 0; j < n; ++j) {
+            const int k = m + 2 * j + 1;
+            const long double b1 = beta(k + 1), b2 = beta(k + 2), i0 = 1.0L / b0, i1 = 1.0L / b1;
+            pe1[j] = (double)(c1 * i0);
+            pe2[j] = (double)(c1 * i1);
+            po[j] = (double)c1;
+            const long double h = i1 / b2, hinv = b1 * b2;
+            const long double c2 = j == 0 ? 1.0L : h0 * hinv * c0;  // C_{j+1}
+            if (j + 1 < n) {
+                const long double a = c1 / c2 * hinv;
+                ra[j + 1] = (double)a;
+                rb[j + 1] = (double)(-a * (i0 * i0 + i1 * i1));
+            }
+            c0 = c1;
+            c1 = c2;
+            h0 = h;
+            b0 = b2;
+        }
+    }
+    auto beta = [m](int l) {
+        const double L = l, M = m;
+        return std::sqrt((4.0 * L * L - 1.0) / (L * L - M * M));
+    };
+    long double c0 = 1.0L, c1 = 1.0L;
+    double b0 = beta(m + 1), rho0 = 0.0;  // beta_k, rho_k (rho_{m+1} is never used)
+    for (int j = 0; j + 1 < n; ++j) {
+        const int k = m + 2 * j + 1;
+        const double b1 = beta(k + 1), b2 = beta(k + 2), rho1 = b1 / b0, rho2 = b2 / b1;
+        const long double v = (long double)b2 * rho1 / b0;
+        const long double c2 = j == 0 ? 1.0L : v * rho0 * c0;  // differs from the C_{j+1} above by a few 1e-15 at most
+        const long double f = c1 / c2, a = (long double)b2 * b1 * f;
+        rbp[j + 1] = (double)(a - (v + rho2) * f);
+        c0 = c1;
+        c1 = c2;
+        b0 = b2;
+        rho0 = rho2;
+    }
+}
+
 // The caches are created on first use and never destroyed at process exit
 // (their destructors would call into the HIP runtime after it has gone);
 // sht_shutdown empties them.  Tables are built outside the cache lock (a
@@ -267,28 +332,36 @@ static int build_coef(int dev, int lmax, int mmax, std::shared_ptr<CoefTables> *
     auto t = std::make_shared<CoefTables>();
     t->dev = dev;
     const int64_t na = nalm_of(lmax, mmax);
-    std::vector<double> alpha(na), cfac(na), mu(mmax + 1);
+    std::vector<double> alpha(na), cfac(na), seed(mmax + 1);
+    const int64_t nj = jcol_base(lmax, mmax + 1);
+    std::vector<double> ra(nj), rb(nj), rbp(nj), pe1(nj), pe2(nj), po(nj);
     for (int m = 0; m <= mmax; ++m) {
         const int64_t b = (int64_t)m * (2 * (int64_t)lmax + 1 - m) / 2 + m;
         coef_column(lmax, m, alpha.data() + b, cfac.data() + b);
+        const int64_t jb = jcol_base(lmax, m);
+        x2_column(lmax, m, ra.data() + jb, rb.data() + jb, rbp.data() + jb, pe1.data() + jb, pe2.data() + jb, po.data() + jb);
     }
-    // mu_m of eq. pmm: mu_0 = 1/sqrt(4 pi), mu_m = mu_{m-1} sqrt((2m+1)/(2m))
+    // mu_m of eq. pmm: mu_0 = 1/sqrt(4 pi), mu_m = mu_{m-1} sqrt((2m+1)/(2m));
+    // q_0 = r_0 = lambda_{m+1,m} / x = sqrt(2m+3) lambda_mm (eq. pm1m)
     long double v = 1.0L / sqrtl(4.0L * 3.141592653589793238462643383279502884L);
-    mu[0] = (double)v;
-    for (int m = 1; m <= mmax; ++m) {
-        v *= sqrtl((long double)(2 * m + 1) / (long double)(2 * m));
-        mu[m] = (double)v;
+    for (int m = 0; m <= mmax; ++m) {
+        if (m > 0) v *= sqrtl((long double)(2 * m + 1) / (long double)(2 * m));
+        seed[m] = (double)(v * sqrtl((long double)(2 * m + 3)));
     }
     t->lmax = lmax;
     t->mmax = mmax;
     t->nalm = na;
     alpha.resize(na + kCoefPad, 0.0);  // kernels may read past the last column
+    for (auto *t2 : {&ra, &rb, &rbp}) t2->resize(nj + kCoefPad, 0.0);
     std::vector<int64_t> mxofs(mmax + 2, 0);
     for (int m = 0; m <= mmax; ++m) mxofs[m + 1] = mxofs[m] + mx_blocks(lmax, m);
     t->mxblocks = mxofs[mmax + 1];
     int rc;
     if ((rc = upload(alpha, &t->alpha, t->owned)) || (rc = upload(cfac, &t->cfac, t->owned)) ||
-        (rc = upload(mu, &t->mu, t->owned)) || (rc = upload(mxofs, &t->mxofs, t->owned)))
+        (rc = upload(ra, &t->ra, t->owned)) || (rc = upload(rb, &t->rb, t->owned)) || (rc = upload(rbp, &t->rbp, t->owned)) ||
+        (rc = upload(pe1, &t->pe1, t->owned)) ||
+        (rc = upload(pe2, &t->pe2, t->owned)) || (rc = upload(po, &t->po, t->owned)) ||
+        (rc = upload(seed, &t->seed, t->owned)) || (rc = upload(mxofs, &t->mxofs, t->owned)))
         return rc;  // t frees what was uploaded
     *out = std::move(t);
     return SHT_OK;
@@ -546,44 +619,61 @@ static bool same_geom(const HostGeom &a, const HostGeom &b) {
 // pi - theta_n (once, or as double(pi) - theta_n) is within it, and a ring any
 // further off mirror is its own slot, evaluated at its own colatitude.
 constexpr long double kMirrorTol = 0x1p-50L;  // 2 ulp of pi = 8.9e-16 rad
-static void build_slots(const HostGeom &h, std::vector<double> &sx, std::vector<double> &ss,
-                        std::vector<int32_t> &sn, std::vector<int32_t> &sso) {
+struct SlotTables {
+    std::vector<double> x, w;  // cos(theta), argument of the x^2 recurrence
+    std::vector<double2> s;    // sin(theta) in two doubles
+    std::vector<int32_t> north, south;
+    int npolar = 0;
+    int size() const { return (int)x.size(); }
+};
+static SlotTables build_slots(const HostGeom &h) {
     const int n = h.nrings;
     std::vector<int> ord(n);
     for (int r = 0; r < n; ++r) ord[r] = r;
     std::sort(ord.begin(), ord.end(), [&](int a, int b) {
         return h.theta[a] < h.theta[b] || (h.theta[a] == h.theta[b] && a < b);
     });
-    struct S { double x, s; int n, so; };
+    struct S { double s; int n, so; };
     std::vector<S> slots;
     int i = 0, j = n - 1;
     while (i <= j) {
         const int a = ord[i], b = ord[j];
         if (i == j) {
-            slots.push_back({std::cos(h.theta[a]), std::sin(h.theta[a]), a, -1});
+            slots.push_back({std::sin(h.theta[a]), a, -1});
             break;
         }
         const long double d = ((long double)h.theta[a] + (long double)h.theta[b]) - kPiL;
         if (fabsl(d) <= kMirrorTol) {
-            slots.push_back({std::cos(h.theta[a]), std::sin(h.theta[a]), a, b});
+            slots.push_back({std::sin(h.theta[a]), a, b});
             ++i;
             --j;
         } else if (d < 0) {
-            slots.push_back({std::cos(h.theta[a]), std::sin(h.theta[a]), a, -1});
+            slots.push_back({std::sin(h.theta[a]), a, -1});
             ++i;
         } else {
-            slots.push_back({std::cos(h.theta[b]), std::sin(h.theta[b]), b, -1});
+            slots.push_back({std::sin(h.theta[b]), b, -1});
             --j;
         }
     }
     // polar slots first: neighbouring lanes then leave the rescaled regime together
     std::stable_sort(slots.begin(), slots.end(), [](const S &p, const S &q) { return p.s < q.s; });
+    SlotTables t;
+    int near_pole = 0;
+    for (const S &s : slots) near_pole += s.s * s.s < 0.5;
+    t.npolar = near_pole < kPolarSlots ? 0 : kPolarSlots;
     for (const S &s : slots) {
-        sx.push_back(s.x);
-        ss.push_back(s.s);
-        sn.push_back(s.n);
-        sso.push_back(s.so);
+        const long double th = h.theta[s.n], sn = sinl(th);
+        const double c = std::cos(h.theta[s.n]);
+        // the polar half of the polar slots is evaluated at cos(theta) rounded
+        // to a double, the others at cos(theta)^2 itself, rounded once
+        const long double cl = (int)t.w.size() < t.npolar / 2 ? (long double)c : cosl(th), c2 = cl * cl;
+        t.w.push_back((int)t.w.size() < t.npolar ? (double)(c2 - 1.0L) : (double)c2);
+        t.x.push_back(c);
+        t.s.push_back(make_double2((double)sn, (double)(sn - (long double)(double)sn)));
+        t.north.push_back(s.n);
+        t.south.push_back(s.so);
     }
+    return t;
 }
 
 // The slot count depends on the colatitudes only; the last few results are
@@ -596,10 +686,7 @@ int count_slots(const HostGeom &h) {
         for (const auto &e : memo)
             if (e.first == h.theta) return e.second;
     }
-    std::vector<double> sx, ss;
-    std::vector<int32_t> sn, sso;
-    build_slots(h, sx, ss, sn, sso);
-    const int n = (int)sx.size();
+    const int n = build_slots(h).size();
     std::lock_guard<std::mutex> lk(mu);
     if (memo.size() >= 256) memo.erase(memo.begin());
     memo.emplace_back(h.theta, n);
@@ -657,10 +744,9 @@ static int build_geom(int dev, const HostGeom &hg, std::shared_ptr<GeomPlan> *ou
     p.dev = dev;
     p.nrings = hg.nrings;
     p.npix = hg.npix;
-    std::vector<double> sx, ss;
-    std::vector<int32_t> sn, sso;
-    build_slots(hg, sx, ss, sn, sso);
-    p.nslots = (int)sx.size();
+    const SlotTables slots = build_slots(hg);
+    p.nslots = slots.size();
+    p.npolar = slots.npolar;
     std::vector<FftDesc> descs;
     std::map<int, int> desc_index;
     std::vector<int32_t> ring_desc(hg.nrings);
@@ -699,8 +785,8 @@ static int build_geom(int dev, const HostGeom &hg, std::shared_ptr<GeomPlan> *ou
     // FFT jobs: mirror pairs with equal nphi, then leftover rings paired by length
     std::vector<int2> jobs;
     std::vector<char> used(hg.nrings, 0);
-    for (size_t i = 0; i < sn.size(); ++i) {
-        const int a = sn[i], b = sso[i];
+    for (int i = 0; i < slots.size(); ++i) {
+        const int a = slots.north[i], b = slots.south[i];
         if (b >= 0 && hg.nphi[a] == hg.nphi[b]) {
             jobs.push_back(make_int2(a, b));
             used[a] = used[b] = 1;
@@ -730,8 +816,9 @@ static int build_geom(int dev, const HostGeom &hg, std::shared_ptr<GeomPlan> *ou
         if (cls[c].empty()) continue;
         if ((rc = upload(cls[c], &p.class_jobs[c], p.owned))) return rc;
     }
-    if ((rc = upload(sx, &p.slot_x, p.owned)) || (rc = upload(ss, &p.slot_s, p.owned)) ||
-        (rc = upload(sn, &p.slot_north, p.owned)) || (rc = upload(sso, &p.slot_south, p.owned)) ||
+    if ((rc = upload(slots.x, &p.slot_x, p.owned)) || (rc = upload(slots.w, &p.slot_w, p.owned)) ||
+        (rc = upload(slots.s, &p.slot_s, p.owned)) || (rc = upload(slots.north, &p.slot_north, p.owned)) ||
+        (rc = upload(slots.south, &p.slot_south, p.owned)) ||
         (rc = upload(hg.phi0, &p.phi0, p.owned)) || (rc = upload(hg.ofs, &p.ofs, p.owned)) ||
         (rc = upload(ring_desc, &p.ring_desc, p.owned)) || (rc = upload(descs, &p.descs, p.owned)))
         return rc;
@@ -768,10 +855,10 @@ int get_start(const CoefTables &c, const GeomRef &pref, hipStream_t st, StartRef
     const size_t n = (size_t)(c.mmax + 1) * (size_t)p.nslots;
     void *a = nullptr, *b = nullptr;
     if (!dev_alloc(&a, n * sizeof(int32_t))) return SHT_ENOMEM;
-    t->lstart = static_cast<int32_t *>(a);
-    if (!dev_alloc(&b, n * sizeof(double2))) return SHT_ENOMEM;  // t frees lstart
+    t->jstart = static_cast<int32_t *>(a);
+    if (!dev_alloc(&b, n * sizeof(double2))) return SHT_ENOMEM;  // t frees jstart
     t->state = static_cast<double2 *>(b);
-    int rc = launch_leg_start(c, p, t->lstart, t->state, st);
+    int rc = launch_leg_start(c, p, t->jstart, t->state, st);
     if (rc == SHT_OK && hipStreamSynchronize(st) != hipSuccess) rc = SHT_EDEVICE;
     if (rc) return rc;
     std::vector<std::shared_ptr<StartTable>> dropped;  // freed after the lock is released
