@@ -83,3 +83,42 @@ def test_batch_tiles_with_polar_slots(nslots, tile):
     ref = oracle.map2alm(lmax, lmax, g, s)
     assert relrms(got, ref) <= TOL, relrms(got, ref)
     assert np.array_equal(mp, sht.alm2map(torch.from_numpy(a).cuda(), g, lmax).cpu().numpy())
+
+
+@pytest.mark.parametrize("nslots,nmaps", [(65, 3), (255, 4), (256, 5), (257, 6), (512, 9), (513, 4), (769, 5), (1024, 3),
+                                          (1025, 4), (1537, 6), (2048, 4), (2049, 3), (2049, 5), (4097, 4)])
+def test_many_maps(nslots, nmaps):
+    """Analysis of several maps: sets per wave, workgroups per m and maps left
+    over, every map a different one."""
+    import torch
+    import paper_1106_0159_amd as sht
+    for polar, lmax, mmax in ((False, 37, 37), (True, 30, 11), (True, 4, 4)):
+        g = rings(nslots, 300 + nslots, polar)
+        s = np.stack([si.random_map(g, 10 * nslots + k) for k in range(nmaps)])
+        say(f"many maps: {nslots} slots polar={polar} lmax={lmax} mmax={mmax} nmaps={nmaps}")
+        al = sht.map2alm(torch.from_numpy(s).cuda(), g, lmax, mmax).cpu().numpy()
+        for k in range(nmaps):
+            ref = oracle.map2alm(lmax, mmax, g, s[k])
+            assert relrms(al[k], ref) <= TOL, (nslots, polar, lmax, k, relrms(al[k], ref))
+
+
+def test_many_maps_infinite_ring():
+    """An infinite pixel stays in its map, and out of the columns and degrees
+    before its ring's start, as with one map."""
+    import torch
+    import paper_1106_0159_amd as sht
+    g = rings(300, 11, False)
+    s = np.stack([si.random_map(g, k) for k in range(4)])
+    s[1, 0] = np.inf  # a pixel of the ring nearest the pole
+    al = sht.map2alm(torch.from_numpy(s).cuda(), g, 400).cpu().numpy()
+    one = sht.map2alm(torch.from_numpy(s[1:2]).cuda(), g, 400).cpu().numpy()
+    for k in (0, 2, 3):
+        assert relrms(al[k], oracle.map2alm(400, 400, g, s[k])) <= TOL
+    assert np.isfinite(one).any() and not np.isfinite(one).all()
+    # a set of 64 slots shares its first start: other degrees may be lost only
+    # in the orders in which the ring has a term at all
+    for m in range(401):
+        base = m * (2 * 400 + 1 - m) // 2
+        col = slice(base + m, base + 401)
+        if np.isfinite(one[0][col]).all():
+            assert np.isfinite(al[1][col]).all(), m
