@@ -19,11 +19,11 @@
 // length (8, 4, 2, 3, 5, then any larger prime as a direct R-term stage); each
 // stage reads its butterflies into registers, synchronises, and writes them
 // back.  Lengths whose larger prime factors would make those direct stages
-// costly use Bluestein's chirp-z identity instead (when 2N-1 rounds up to a
-// 5-smooth length that fits)
-//   X_k = conj(b_k) sum_n (x_n conj(b_n)) b_{k-n},  b_t = e^{i pi t^2/N},
-// as a cyclic convolution of 5-smooth length L >= 2N-1 done with two forward
-// transforms (the filter spectrum, scaled by 1/L, is a plan table).
+// costly use Bluestein's chirp-z identity instead
+//   X_k = conj(b_k) sum_n (x_n conj(b_n)) b_{k-n},  b_t = e^{i pi t^2/n},
+// as a cyclic convolution of length L >= 2n - 2, a class's own length, done
+// with two forward transforms (the filter spectrum, scaled by 1/L, is a plan
+// table); rings of even length N go one at a time, as n = N/2 complex points.
 #include <type_traits>
 
 #include "k_device.h"
@@ -198,11 +198,6 @@ __device__ __forceinline__ void butterfly(double2 (&v)[R]) {
 // the tables and its other twiddles as powers of it (at most R - 2 further
 // products, a few ulp for R <= 8).
 constexpr int kTwLo = 64;
-// LDS index of point x (unpadded: a slot after every 8 points, meant to
-// spread the strided Stockham writes over the banks, timed slower on gfx950)
-__device__ __forceinline__ int pd(int x) { return x; }
-template <int L>
-constexpr int padded_len() { return L; }
 template <int MAXL>
 constexpr int tw_entries() { return kTwLo + (MAXL + kTwLo - 1) / kTwLo; }
 
@@ -231,11 +226,11 @@ __device__ __forceinline__ void load_twiddles(double2 *lo, double2 *hi, const do
 // points in registers (no LDS pass and no barrier for them).
 struct LdsIn {
     const double2 *buf;
-    __device__ __forceinline__ double2 operator()(int t) const { return buf[pd(t)]; }
+    __device__ __forceinline__ double2 operator()(int t) const { return buf[t]; }
 };
 struct LdsOut {
     double2 *buf;
-    __device__ __forceinline__ void operator()(int t, double2 v) const { buf[pd(t)] = v; }
+    __device__ __forceinline__ void operator()(int t, double2 v) const { buf[t] = v; }
 };
 
 // FIRST: the first stage (Ns = 1, all twiddles 1); a stage with register
@@ -263,7 +258,7 @@ __device__ __forceinline__ void fft_stage(double2 *buf, int L, int Ns_, TwLds tw
             double2 wr = w1;
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                const double2 xv = kLdsIn ? buf[pd(j + r * nbf)] : in(j + r * nbf);
+                const double2 xv = kLdsIn ? buf[j + r * nbf] : in(j + r * nbf);
                 if (r == 0 || kFirst) {
                     v[b][r] = xv;
                 } else {
@@ -285,7 +280,7 @@ __device__ __forceinline__ void fft_stage(double2 *buf, int L, int Ns_, TwLds tw
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 if (kLdsOut)
-                    buf[pd(o + r * Ns)] = v[b][r];
+                    buf[o + r * Ns] = v[b][r];
                 else
                     out(o + r * Ns, v[b][r]);
             }
@@ -325,10 +320,10 @@ __device__ __forceinline__ void fft_stage_generic(double2 *buf, int L, int Ns, i
         const int j = i - (q - 1) * nbf;
         const int jq = (int)(((float)j + 0.5f) * inv_ns);
         const int kt = (j - jq * Ns) * tstep;  // k tstep < L / R: q kt < L
-        const double2 a = cmul(buf[pd(j + q * nbf)], tw(q * kt));
-        const double2 b = cmul(buf[pd(j + (R - q) * nbf)], tw((R - q) * kt));
-        buf[pd(j + q * nbf)] = add2(a, b);
-        buf[pd(j + (R - q) * nbf)] = sub2(a, b);
+        const double2 a = cmul(buf[j + q * nbf], tw(q * kt));
+        const double2 b = cmul(buf[j + (R - q) * nbf], tw((R - q) * kt));
+        buf[j + q * nbf] = add2(a, b);
+        buf[j + (R - q) * nbf] = sub2(a, b);
     }
     __syncthreads();
     // pass 2: item i = (group g, butterfly j); group g holds s = 2 g, 2 g + 1 (<= h)
@@ -340,7 +335,7 @@ __device__ __forceinline__ void fft_stage_generic(double2 *buf, int L, int Ns, i
         if (i >= nbf * ng) break;
         const int g = (int)(((float)i + 0.5f) * inv_nbf);
         const int j = i - g * nbf;
-        const double2 x0 = buf[pd(j)];
+        const double2 x0 = buf[j];
         double2 A[kPairs], Bp[kPairs], w[kPairs], ws[kPairs];
 #pragma unroll
         for (int u = 0; u < kPairs; ++u) {
@@ -357,7 +352,7 @@ __device__ __forceinline__ void fft_stage_generic(double2 *buf, int L, int Ns, i
             }
             const int qe = min(h, q0 + kAnchor - 1);
             for (int q = q0; q <= qe; ++q) {
-                const double2 P = buf[pd(j + q * nbf)], M = buf[pd(j + (R - q) * nbf)];
+                const double2 P = buf[j + q * nbf], M = buf[j + (R - q) * nbf];
 #pragma unroll
                 for (int u = 0; u < kPairs; ++u) {
                     // A += cos t P, B' += -sin t M = w.y M  (so B = -B')
@@ -389,8 +384,8 @@ __device__ __forceinline__ void fft_stage_generic(double2 *buf, int L, int Ns, i
         for (int u = 0; u < kPairs; ++u) {
             const int sv = kPairs * g + u;
             if (sv > h) break;
-            buf[pd(o + sv * Ns)] = y[it][2 * u];
-            if (sv > 0) buf[pd(o + (R - sv) * Ns)] = y[it][2 * u + 1];
+            buf[o + sv * Ns] = y[it][2 * u];
+            if (sv > 0) buf[o + (R - sv) * Ns] = y[it][2 * u + 1];
         }
     }
     __syncthreads();
@@ -429,8 +424,7 @@ __device__ __forceinline__ void fft_stages(double2 *buf, DescP d, TwLds tw, int 
 }
 
 // DFT of n points: afterwards X_k is result_at(buf, d, k).  The points are those
-// already placed in buf[0..n) (pre-multiplied by conj(chirp) when Bluestein),
-// or, when in_reg and reg_first(d), in(t) for t < L = n, read by the first
+// already placed in buf[0..n), or, when in_reg and reg_first(d), in(t) for t < L = n, read by the first
 // stage.  With out_reg and reg_last(d) the last stage hands X_t to out(t, X_t)
 // instead (t < n), and buf holds no result.  (The register stages sit outside
 // the stage loop, so that the compiler keeps none of their addresses live
@@ -439,7 +433,7 @@ template <int MAXL, int NT, class In = LdsIn, class Out = LdsOut>
 __device__ __forceinline__ void transform(double2 *buf, DescP d, TwLds tw, In in = In{}, bool in_reg = false,
                                           Out out = Out{}, bool out_reg = false) {
     constexpr bool kRegIn = !std::is_same<In, LdsIn>::value, kRegOut = !std::is_same<Out, LdsOut>::value;
-    const int L = d->L, nrad = d->nrad, passes = d->bluestein ? 2 : 1;
+    const int L = d->L, nrad = d->nrad;
     in_reg = kRegIn && in_reg && reg_first(d);
     out_reg = kRegOut && out_reg && reg_last(d);
     int s0 = 0, Ns0 = 1;
@@ -453,23 +447,7 @@ __device__ __forceinline__ void transform(double2 *buf, DescP d, TwLds tw, In in
                 fft_stage<4, MAXL, NT, true, In, LdsOut>(buf, L, 1, tw, in, LdsOut{buf});
         }
     }
-    const int s1 = out_reg ? nrad - 1 : nrad;
-    // Bluestein (no register stages): zero padding, then two transforms with
-    // one copy of the stage code (the kernels are otherwise large enough to
-    // thrash the instruction cache)
-    const double2 *__restrict__ kern = d->kern;
-    if (passes == 2) {
-        for (int t = d->n + threadIdx.x; t < L; t += NT) buf[pd(t)] = make_double2(0.0, 0.0);
-        __syncthreads();
-    }
-#pragma unroll 1
-    for (int pass = 0; pass < passes; ++pass) {
-        if (pass == 1) {
-            for (int t = threadIdx.x; t < L; t += NT) buf[pd(t)] = conj2(cmul(buf[pd(t)], kern[t]));
-            __syncthreads();
-        }
-        fft_stages<MAXL, NT>(buf, d, tw, pass == 0 ? s0 : 0, pass == passes - 1 ? s1 : nrad, pass == 0 ? Ns0 : 1);
-    }
+    fft_stages<MAXL, NT>(buf, d, tw, s0, out_reg ? nrad - 1 : nrad, Ns0);
     if constexpr (kRegOut) {
         if (out_reg) {
             const int R = d->rad[nrad - 1];
@@ -479,6 +457,147 @@ __device__ __forceinline__ void transform(double2 *buf, DescP d, TwLds tw, In in
                 fft_stage<4, MAXL, NT, false, LdsIn, Out>(buf, L, L / 4, tw, LdsIn{buf}, out);
         }
     }
+}
+
+// ---------------------------------------------------------------- power-of-two lengths
+// The length of a class itself (1024, 2048, 4096, 8192: the equatorial belts
+// of the power-of-two HEALPix grids, and Bluestein's L for many Gauss-Legendre
+// grids) has a transform of its own with every stage's radix and stride known
+// at compile time: addresses are immediates and powers of two instead of
+// products and reciprocals, and the points of LDS are swizzled so that no
+// access conflicts.  In natural order the first stage's writes (a lane's
+// points 8 apart, 128 bytes) hit every bank eight times over, a quarter of the
+// time of a 4096-point job.  Bound: LDS bandwidth and the FP64 units together.
+// 64 maps of 1025 rings of 2049 points (Bluestein on 4096): synthesis 1.79 ms
+// with the general stages, 1.17 with these; a HEALPix 1024 belt (2049 rings of
+// 4096, one map) 58 and 45 us.  lds_swz permutes each aligned run of 16 points
+// (256 bytes, all banks): it is linear over xor, so an index whose parts occupy
+// different bits splits into a lane's base and a constant.
+__host__ __device__ constexpr int lds_swz(int x) {
+    return x ^ ((x >> 4) & 7) ^ ((((x >> 5) ^ (x >> 6)) & 1) << 3);
+}
+// index of point x with the swizzle on (mask 15) or off (0)
+__device__ __forceinline__ int lds_at(int x, int mask) { return x ^ ((x ^ lds_swz(x)) & mask); }
+
+// The stages' radices: 8 first and last, so that the last stage's outputs of a
+// thread are the first stage's inputs (points j + r L/8).
+template <int L>
+struct Pow2Radix;
+template <>
+struct Pow2Radix<1024> {
+    static constexpr int n = 4, r[4] = {8, 4, 4, 8};
+};
+template <>
+struct Pow2Radix<2048> {
+    static constexpr int n = 4, r[4] = {8, 4, 8, 8};
+};
+template <>
+struct Pow2Radix<4096> {
+    static constexpr int n = 4, r[4] = {8, 8, 8, 8};
+};
+template <>
+struct Pow2Radix<8192> {
+    static constexpr int n = 5, r[5] = {8, 4, 4, 8, 8};
+};
+template <int L>
+constexpr int pow2_ns(int s) { return s == 0 ? 1 : pow2_ns<L>(s - 1) * Pow2Radix<L>::r[s - 1]; }
+
+// inputs of butterfly j (stride L/R), twiddled, and its outputs, in registers
+template <int L, int R, int Ns>
+__device__ __forceinline__ void pow2_load(const double2 *buf, int j, TwLds tw, double2 (&v)[R]) {
+    constexpr int nbf = L / R, tstep = L / (Ns * R);
+    static_assert(nbf >= 128, "r nbf lies above the swizzled bits");
+    const double2 *p = buf + lds_swz(j);
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = p[r * nbf];
+    const int t = (j & (Ns - 1)) * tstep;
+    const double2 w1 = tstep % kTwLo == 0 ? tw.hi[t / kTwLo] : tw(t);
+    const double2 w2 = cmul(w1, w1), w3 = cmul(w2, w1);
+    v[1] = cmul(v[1], w1);
+    v[2] = cmul(v[2], w2);
+    v[3] = cmul(v[3], w3);
+    if constexpr (R == 8) {
+        const double2 w4 = cmul(w2, w2);
+        v[4] = cmul(v[4], w4);
+        v[5] = cmul(v[5], cmul(w4, w1));
+        v[6] = cmul(v[6], cmul(w3, w3));
+        v[7] = cmul(v[7], cmul(w4, w3));
+    }
+    butterfly<R>(v);
+}
+template <int R, int Ns>
+__device__ __forceinline__ void pow2_store(double2 *buf, int j, const double2 (&v)[R]) {
+    const int k = j & (Ns - 1), o = lds_swz((j - k) * R + k);
+#pragma unroll
+    for (int r = 0; r < R; ++r) buf[o ^ lds_swz(r * Ns)] = v[r];
+}
+// stage s (not the first, not the last) in place
+template <int L, int NT, int S>
+__device__ __forceinline__ void pow2_stage(double2 *buf, TwLds tw) {
+    constexpr int R = Pow2Radix<L>::r[S], Ns = pow2_ns<L>(S), nbf = L / R, B = nbf > NT ? nbf / NT : 1;
+    double2 v[B][R];
+#pragma unroll
+    for (int b = 0; b < B; ++b)
+        if (nbf >= NT || (int)threadIdx.x < nbf) pow2_load<L, R, Ns>(buf, threadIdx.x + b * NT, tw, v[b]);
+    __syncthreads();  // in place: every read is done before the writes
+#pragma unroll
+    for (int b = 0; b < B; ++b)
+        if (nbf >= NT || (int)threadIdx.x < nbf) pow2_store<R, Ns>(buf, threadIdx.x + b * NT, v[b]);
+    __syncthreads();
+}
+// As transform() for d->L == L (points and result swizzled in buf).  Under
+// Bluestein the points past n are taken as zero, and the last stage of the
+// first pass, the product with the filter and the first stage of the second
+// pass are one step in registers.
+template <int L, int NT, class In = LdsIn, class Out = LdsOut>
+__device__ __forceinline__ void transform_pow2(double2 *buf, DescP d, TwLds tw, In in = In{}, Out out = Out{}) {
+    constexpr bool kRegIn = !std::is_same<In, LdsIn>::value, kRegOut = !std::is_same<Out, LdsOut>::value;
+    constexpr int n = Pow2Radix<L>::n, nbf = L / 8;
+    static_assert(nbf <= NT && Pow2Radix<L>::r[0] == 8 && Pow2Radix<L>::r[n - 1] == 8, "one butterfly per thread");
+    const bool blue = d->bluestein != 0, act = nbf == NT || (int)threadIdx.x < nbf;
+    const int passes = blue ? 2 : 1, j = threadIdx.x;
+    const double2 *__restrict__ kern = d->kern;
+    double2 v[8];
+    if (act) {
+        if (kRegIn && !blue) {
+#pragma unroll
+            for (int r = 0; r < 8; ++r) v[r] = in(j + r * nbf);
+        } else {
+            const int lim = d->n;
+            const double2 *p = buf + lds_swz(j);
+#pragma unroll
+            for (int r = 0; r < 8; ++r) v[r] = j + r * nbf < lim ? p[r * nbf] : make_double2(0.0, 0.0);
+        }
+        butterfly<8>(v);
+    }
+    if (!kRegIn || blue) __syncthreads();  // in place: every read is done before the writes
+#pragma unroll 1
+    for (int pass = 0;; ++pass) {
+        if (act) pow2_store<8, 1>(buf, j, v);
+        __syncthreads();
+        pow2_stage<L, NT, 1>(buf, tw);
+        pow2_stage<L, NT, 2>(buf, tw);
+        if constexpr (n == 5) pow2_stage<L, NT, 3>(buf, tw);
+        if (act) pow2_load<L, 8, nbf>(buf, j, tw, v);
+        if (pass + 1 == passes) break;
+        if (act) {
+#pragma unroll
+            for (int r = 0; r < 8; ++r)  // the filter is even: kern[L - t] = kern[t]
+                v[r] = conj2(cmul(v[r], kern[r < 4 ? j + r * nbf : L - j - r * nbf]));
+            butterfly<8>(v);
+        }
+        __syncthreads();
+    }
+    if (kRegOut && !blue) {
+        if (act) {
+#pragma unroll
+            for (int r = 0; r < 8; ++r) out(j + r * nbf, v[r]);
+        }
+        return;
+    }
+    __syncthreads();
+    if (act) pow2_store<8, nbf>(buf, j, v);
+    __syncthreads();
 }
 
 // Bluestein chirp b_t = e^{i pi t^2 / n}.  The angle's numerator q = t^2
@@ -511,6 +630,7 @@ struct Chirp {
         q = q < 0 ? q + n2 : (q >= n2 ? q - n2 : q);
         return cmul(hi[q / kChLo], lo[q % kChLo]);
     }
+    __device__ __forceinline__ double2 turn(int r) const { return cmul(hi[r / kChLo], lo[r % kChLo]); }  // e^{i pi r / n}, r < 2n
 };
 // fills the chirp tables of length n (caller synchronises)
 template <int NT>
@@ -525,10 +645,11 @@ __device__ __forceinline__ Chirp load_chirp(double2 *lo, double2 *hi, int n) {
     return Chirp{lo, hi, n, 1.0 / (2.0 * (double)n)};
 }
 
-__device__ __forceinline__ double2 result_at(const double2 *buf, DescP d, const Chirp &ch, int k) {
-    if (!d->bluestein) return buf[pd(k)];
+__device__ __forceinline__ double2 result_at(const double2 *buf, DescP d, const Chirp &ch, int k, int swz) {
+    const double2 v = buf[lds_at(k, swz)];
+    if (!d->bluestein) return v;
     // X_k = conj(b_k) * conj(y_k), y = conj(second transform)
-    return conj2(cmul(ch(k), buf[pd(k)]));
+    return conj2(cmul(ch(k), v));
 }
 
 __device__ __forceinline__ double2 input_point(double2 v, DescP d, const Chirp &ch, int t) {
@@ -574,35 +695,48 @@ __device__ __forceinline__ double2 bin_term(double2 dv, int m, const Phase &ph) 
     return make_double2(2.0 * fma(dv.x, e.x, -dv.y * e.y), 2.0 * fma(dv.x, e.y, dv.y * e.x));
 }
 
-// c_k of one ring: sum over m = k mod n (m <= mmax) of w_m Delta_m e^{i m phi0},
-// in increasing m, given the term of m = k (first, zero if k > mmax)
-__device__ __forceinline__ double2 fold_bin(double2 first, const double2 *__restrict__ D, int64_t sm, int k, int n,
+// first + sum over m = m0, m0 + step, .. <= mmax of w_m Delta_m e^{i m phi0},
+// in increasing m (m0 > 0), four loads in flight
+__device__ __forceinline__ double2 fold_sum(double2 first, const double2 *__restrict__ D, int64_t sm, int m0, int step,
                                             int mmax, const Phase &ph) {
     double cr = first.x, ci = first.y;
-    for (int m = k + n; m <= mmax; m += n) {
-        const double2 t = bin_term(D[m * sm], m, ph);
-        cr += t.x;
-        ci += t.y;
+#pragma unroll 1
+    for (int m = m0; m <= mmax; m += 4 * step) {
+        double2 v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            v[i] = m + i * step <= mmax ? D[(m + i * step) * sm] : make_double2(0.0, 0.0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (m + i * step <= mmax) {
+                const double2 t = bin_term(v[i], m + i * step, ph);
+                cr += t.x;
+                ci += t.y;
+            }
+        }
     }
     return make_double2(cr, ci);
 }
-
-// phased terms of one ring for m = tid, tid+NT, ...: w_m Delta_m e^{i m phi0}
-template <int NT>
-__device__ __forceinline__ void phased_terms(const double2 *__restrict__ D, int64_t sm, int mmax, const Phase &ph,
-                                             double2 *__restrict__ out) {
-    for (int m = threadIdx.x; m <= mmax; m += NT) {
-        const double2 dv = D[m * sm];
-        if (m == 0) {
-            out[0] = make_double2(dv.x, 0.0);
-        } else {
-            const double2 e = ph(m);
-            out[m] = make_double2(2.0 * fma(dv.x, e.x, -dv.y * e.y), 2.0 * fma(dv.x, e.y, dv.y * e.x));
-        }
-    }
+// c_k of one ring: sum over m = k mod n (m <= mmax), given the term of m = k
+// (first, zero if k > mmax)
+__device__ __forceinline__ double2 fold_bin(double2 first, const double2 *__restrict__ D, int64_t sm, int k, int n,
+                                            int mmax, const Phase &ph) {
+    return fold_sum(first, D, sm, k + n, n, mmax, ph);
 }
 
-// sum_{m = k mod n, m <= lim} t_m, in increasing m
+// Column sums of a short ring (n <= NT): with S = n * floor(NT / n), thread
+// u < S leaves t_u = sum_{j >= 0} of the terms m = u + jS in LDS.  As S is a
+// multiple of n, c_k is then sum_{i < S/n} t_{k + in}: every thread works on
+// the (mmax+1)/n terms of the few bins.  (Rows of all mmax+1 phased terms
+// instead, two per workgroup, left one workgroup per CU: 153 us for 16 maps on
+// 256 rings of 524 points, mmax 2048.)
+template <int NT>
+__device__ __forceinline__ void fold_columns(double2 *__restrict__ t, const double2 *__restrict__ D, int64_t sm, int n,
+                                             int mmax, const Phase &ph) {
+    const int S = n * (NT / n), u = threadIdx.x;
+    if (u < S && u <= mmax) t[u] = fold_sum(bin_term(D[u * sm], u, ph), D, sm, u + S, S, mmax, ph);
+}
+// c_k from the column sums: sum_{m = k mod n, m <= lim} t_m, in increasing m
 __device__ __forceinline__ double2 fold_terms(const double2 *__restrict__ t, int k, int n, int lim) {
     double cr = 0.0, ci = 0.0;
     for (int m = k; m <= lim; m += n) {
@@ -612,32 +746,13 @@ __device__ __forceinline__ double2 fold_terms(const double2 *__restrict__ t, int
     return make_double2(cr, ci);
 }
 
-// In-place column sums for a short ring (n <= NT): with S = n * floor(NT / n),
-// thread u < S replaces t_u by sum_{j >= 0} t_{u + jS}.  As S is a multiple of
-// n, the bin sum c_k is then sum_{i < S/n} t_{k + in}: two short sums instead
-// of one of (mmax+1)/n terms.  Only thread u reads t_u for u < S, so the
-// update needs no extra buffer.  Returns the last index to fold.
-template <int NT>
-__device__ __forceinline__ int fold_columns(double2 *__restrict__ t, int n, int mmax) {
-    const int S = n * (NT / n);
-    const int u = threadIdx.x;
-    if (u < S && u <= mmax) {
-        double cr = 0.0, ci = 0.0;
-        for (int m = u; m <= mmax; m += S) {
-            cr += t[m].x;
-            ci += t[m].y;
-        }
-        t[u] = make_double2(cr, ci);
-    }
-    return min(S - 1, mmax);
-}
-
 // The two real sequences a workgroup transforms as one complex sequence:
 // ring ra of map ma and ring rb of map mb (rings of equal length).
 struct JobSeqs {
     int ra, rb, ma, mb;
     bool two;  // false: only sequence a
 };
+// (FftDesc::half: sequence a alone, of the ring job.x, with job.y == kHalfJob.)
 // Workgroup -> sequences.  Ring-major Delta: a job (a mirror pair or two
 // rings of equal length) of one map, the maps of one job in consecutive
 // workgroups (they share the job's tables through L2).  Map-minor Delta: one
@@ -662,6 +777,10 @@ __device__ __forceinline__ bool job_seqs(int njobs, int nmaps, int map_minor, co
     const int ma = (rem % groups) * 8 + 2 * (k % 4);
     if (ji >= njobs || ma >= nmaps) return false;
     const int2 job = jobs[ji];
+    if (job.y == kHalfJob) {  // the unit's two rings are the two maps of each pair
+        js = JobSeqs{job.x, job.x, ma + rem / groups, ma + rem / groups, false};
+        return js.ma < nmaps;
+    }
     const int r = rem / groups ? job.y : job.x;
     if (r < 0) return false;
     js = JobSeqs{r, r, ma, ma + 1 < nmaps ? ma + 1 : ma, ma + 1 < nmaps};
@@ -680,7 +799,6 @@ __device__ __forceinline__ bool ring_task(const RingPlan &one, const RingPlan *p
         P.mmax = q->mmax;
         P.nmaps = 1;
         P.njobs = q->njobs;
-        P.fold_rows = q->fold_rows;
         P.ph_tab = q->ph_tab;
         P.npix = q->npix;
         P.dl.s_map = q->dl.s_map;
@@ -714,9 +832,67 @@ inline int64_t fft_grid(int njobs, int nmaps, int map_minor) {
     return (units + 7) / 8 * 32;
 }
 
-// Synthesis.  LDS: the twiddle tables, buf[L], plus (fold_rows != 0) two
-// rows of mmax+1 phased terms used when the ring folds many m per bin,
-// n < (mmax+1)/2.
+// Rings transformed one at a time (FftDesc::half): an even length N as a
+// complex transform of n = N / 2 points under Bluestein, with the even pixels
+// as real and the odd ones as imaginary part.  This halves the convolution's
+// length, so that it fits for every N <= 8192 (synthesis stage of HEALPix 2048 at
+// lmax 4096, whose 2002 rings above 4096 points took direct stages of their
+// primes before: 890 us, now 521) and, at half the LDS, two workgroups share a
+// CU up to N = 4098 instead of one (256 rings of 4 x 1021: 38 us as pairs on
+// 8192 points, 22 on 4096).
+//
+// Synthesis, h the Hermitian spectrum of the ring: with E_k = h_k + conj h_{n-k}
+// and O_k = (h_k - conj h_{n-k}) e^{i pi k / n}, z_t = s_{2t} + i s_{2t+1} =
+// conj FFT(conj(E + i O))_t.  Analysis: S_k = E_k + e^{-i pi k / n} O_k with
+// E_k = (Z_k + conj Z_{n-k}) / 2, O_k = (Z_k - conj Z_{n-k}) / (2i), k <= n.
+// The turns e^{i pi k / n} come from the chirp's own tables.
+// Fold of a synthesis job: the transform's input points conj(E + i O).
+template <int MAXL, int NT>
+__device__ __forceinline__ void half_fold(const double2 *__restrict__ D, int64_t sm, int mmax, int n, const Chirp &ch, const Phase &ph, double2 *buf) {
+    const int N = 2 * n;
+    auto herm = [&](double2 c0, double2 c1) { return make_double2(0.5 * (c0.x + c1.x), 0.5 * (c0.y - c1.y)); };
+#pragma unroll 1
+    for (int k = threadIdx.x; 2 * k <= n; k += NT) {
+        // bins k and N - k, n - k and n + k
+        const int m[4] = {k, k ? N - k : 0, n - k, n + k};
+        double2 t[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) t[i] = m[i] <= mmax ? D[m[i] * sm] : make_double2(0.0, 0.0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (m[i] <= mmax) t[i] = fold_bin(bin_term(t[i], m[i], ph), D, sm, m[i], N, mmax, ph);
+        const double2 a = herm(t[0], t[1]), b = herm(t[2], t[3]);  // h_k, h_{n-k}
+        const double2 E = make_double2(a.x + b.x, a.y - b.y);
+        const double2 O = cmul(make_double2(a.x - b.x, a.y + b.y), ch.turn(k));
+        buf[lds_swz(k)] = cmul(make_double2(E.x - O.y, -E.y - O.x), conj2(ch(k)));
+        if (k && 2 * k != n) buf[lds_swz(n - k)] = cmul(make_double2(E.x + O.y, E.y - O.x), conj2(ch(n - k)));
+    }
+}
+// Delta of an analysis job from the transform's result.
+template <int NT>
+__device__ __forceinline__ void half_terms(double2 *__restrict__ D, int64_t sm, int mmax, double w, DescP d,
+                                           const Chirp &ch, const Phase &ph, const double2 *buf) {
+    const int n = d->n, N = 2 * n;
+#pragma unroll 1
+    for (int m = threadIdx.x; m <= mmax; m += NT) {
+        const int k = m < N ? m : m % N, kk = k <= n ? k : N - k;
+        const double2 Z = result_at(buf, d, ch, kk == n ? 0 : kk, 15);
+        const double2 Zn = result_at(buf, d, ch, kk == 0 || kk == n ? 0 : n - kk, 15);
+        const double2 E = make_double2(0.5 * (Z.x + Zn.x), 0.5 * (Z.y - Zn.y));
+        const double2 O = make_double2(0.5 * (Z.y + Zn.y), -0.5 * (Z.x - Zn.x));
+        double2 S = add2(E, cmul(O, conj2(ch.turn(kk))));
+        if (k > n) S = conj2(S);
+        const double2 r = cmul(S, conj2(ph(m)));
+        D[m * sm] = make_double2(w * r.x, w * r.y);
+    }
+}
+
+// whether the class sums the columns of very short rings (two rows of NT sums behind the points)
+template <int MAXL>
+constexpr bool kColumns = MAXL <= 1024;
+
+// Synthesis.  LDS: the twiddle and chirp tables, MAXL points, the column sums
+// (class 1024), the phase tables.
 template <int MAXL, int NT, bool BATCH>
 __global__ __launch_bounds__(NT, 4) void k_fft_syn(RingPlan one, const RingPlan *__restrict__ plans,
                                                    const int2 *__restrict__ bjobs) {
@@ -726,14 +902,16 @@ __global__ __launch_bounds__(NT, 4) void k_fft_syn(RingPlan one, const RingPlan 
     RingPlan P;
     JobSeqs js;
     if (!ring_task<BATCH>(one, plans, bjobs, P, js)) return;  // whole workgroup
-    const int mmax = P.mmax, fold_rows = P.fold_rows;
+    const int mmax = P.mmax;
     const DeltaLayout dl = P.dl;
     const bool two = js.two;
     const DescP d = ro(P.descs) + P.ring_desc[js.ra];
     const int N = d->n, L = d->L;
+    const int swz = L == MAXL ? 15 : 0;  // points of LDS swizzled
+    const bool half = d->half != 0;  // one sequence of 2 N pixels
     const double2 *__restrict__ Da = P.din + js.ma * dl.s_map + js.ra * dl.s_ring;
     const double2 *__restrict__ Db = P.din + js.mb * dl.s_map + js.rb * dl.s_ring;
-    const bool lds_fold = fold_rows && (2 * N < mmax + 1);
+    const bool lds_fold = kColumns<MAXL> && !half && N <= NT && 2 * N < mmax + 1;
     const double2 z = make_double2(0.0, 0.0);
     // Delta at m = k of every bin k = threadIdx.x + u NT of this thread (both
     // rings): all in flight while the tables are set up
@@ -742,7 +920,7 @@ __global__ __launch_bounds__(NT, 4) void k_fft_syn(RingPlan one, const RingPlan 
 #pragma unroll
     for (int u = 0; u <= U; ++u) {
         const int k = threadIdx.x + u * NT;
-        const bool ok = !lds_fold && 2 * k <= N && k <= mmax;
+        const bool ok = !half && !lds_fold && 2 * k <= N && k <= mmax;
         fa[u] = ok ? Da[k * dl.s_m] : z;
         fb[u] = (ok && two) ? Db[k * dl.s_m] : z;
     }
@@ -751,72 +929,130 @@ __global__ __launch_bounds__(NT, 4) void k_fft_syn(RingPlan one, const RingPlan 
     Chirp ch{clo, chi, N, 0.0};
     if (blue) ch = load_chirp<NT>(clo, chi, N);
     const double pa = P.phi0[js.ra], pb = P.phi0[js.rb];
+    // one phase for both sequences and at most one term per bin: no loops or
+    // branches between the loads and the points
+    const bool plain = !half && N > mmax && pa == pb && (P.ph_tab || pa == 0.0);
     Phase pha{nullptr, nullptr, pa}, phb{nullptr, nullptr, pb};
-    if (P.ph_tab) {
-        double2 *tab = buf + padded_len<MAXL>() + (fold_rows ? 2 * (mmax + 1) : 0);
+    if (P.ph_tab && !(plain && pa == 0.0)) {
+        double2 *tab = buf + MAXL + (kColumns<MAXL> ? 2 * NT : 0);
         pha = load_phases<NT>(tab, mmax, pa);
         phb = pha;
-        if (two && js.rb != js.ra) phb = load_phases<NT>(tab + kPhLo + phase_hi_entries(mmax), mmax, pb);
+        if (two && js.rb != js.ra && pa != pb) phb = load_phases<NT>(tab + kPhLo + phase_hi_entries(mmax), mmax, pb);
     }
     if (P.ph_tab || blue) __syncthreads();  // phase and chirp tables visible
-    int lim = mmax;  // last index of the phased-term rows that the bins fold
-    if (lds_fold) {
-        // all threads evaluate phases; short rings first sum the rows in columns
-        double2 *ta = buf + pd(L), *tb = buf + pd(L) + (mmax + 1);
-        phased_terms<NT>(Da, dl.s_m, mmax, pha, ta);
-        if (two) phased_terms<NT>(Db, dl.s_m, mmax, phb, tb);
-        __syncthreads();
-        if (N <= NT) {
-            lim = fold_columns<NT>(ta, N, mmax);
-            if (two) fold_columns<NT>(tb, N, mmax);
+    if (half) {
+        half_fold<MAXL, NT>(Da, dl.s_m, mmax, N, ch, pha, buf);
+    } else if (plain) {
+        // TURN: phi0 != 0; BOTH: n < 2 mmax, bins take m = n - k too
+        auto fold = [&](auto turn, auto both) {
+            constexpr bool TURN = decltype(turn)::value, BOTH = decltype(both)::value;
+            double2 ga[U + 1], gb[U + 1];  // Delta at n - k
+            if constexpr (BOTH) {
+#pragma unroll
+                for (int u = 0; u <= U; ++u) {
+                    const int k = threadIdx.x + u * NT, kn = N - k;
+                    const bool ok = k > 0 && 2 * k <= N && kn <= mmax;
+                    ga[u] = ok ? Da[kn * dl.s_m] : z;
+                    gb[u] = (ok && two) ? Db[kn * dl.s_m] : z;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u <= U; ++u) {
+                const int k = threadIdx.x + u * NT, kn = k ? N - k : 0;
+                if (2 * k <= N) {
+                    double2 a = fa[u], b = fb[u];  // zero above mmax
+                    if constexpr (TURN) {
+                        const double2 e = pha(min(k, mmax));
+                        a = cmul(a, e);
+                        b = cmul(b, e);
+                    }
+                    // w_m Delta_m e^{i m phi0} / 2 with the real part alone of m = 0
+                    double2 ha = k ? a : make_double2(a.x, 0.0), hb = k ? b : make_double2(b.x, 0.0);
+                    if constexpr (BOTH) {
+                        double2 a1 = ga[u], b1 = gb[u];
+                        if constexpr (TURN) {
+                            const double2 e = pha(min(kn, mmax));
+                            a1 = cmul(a1, e);
+                            b1 = cmul(b1, e);
+                        }
+                        if (k) {
+                            ha = make_double2(ha.x + a1.x, ha.y - a1.y);
+                            hb = make_double2(hb.x + b1.x, hb.y - b1.y);
+                        }
+                    } else if (kn == k && k) {  // n = 2 mmax: bin n/2 is its own mirror
+                        ha = make_double2(2.0 * ha.x, 0.0);
+                        hb = make_double2(2.0 * hb.x, 0.0);
+                    }
+                    // conj(g) at k and n - k, g = h_a + i h_b
+                    buf[lds_at(k, swz)] = input_point(make_double2(ha.x - hb.y, -ha.y - hb.x), d, ch, k);
+                    if (kn != k) buf[lds_at(kn, swz)] = input_point(make_double2(ha.x + hb.y, ha.y - hb.x), d, ch, kn);
+                }
+            }
+        };
+        if (pa != 0.0) {
+            if (N < 2 * mmax)
+                fold(std::true_type{}, std::true_type{});
+            else
+                fold(std::true_type{}, std::false_type{});
+        } else {
+            if (N < 2 * mmax)
+                fold(std::false_type{}, std::true_type{});
+            else
+                fold(std::false_type{}, std::false_type{});
+        }
+    } else {
+        double2 *const ta = buf + MAXL, *const tb = ta + NT;  // column sums
+        const int lim = min(N * (NT / N) - 1, mmax);
+        if (lds_fold) {
+            fold_columns<NT>(ta, Da, dl.s_m, N, mmax, pha);
+            if (two) fold_columns<NT>(tb, Db, dl.s_m, N, mmax, phb);
             __syncthreads();
         }
-    }
-    // thread handles the bin pairs (k, n-k), k = threadIdx.x + u NT <= n/2:
-    // u < U for every thread, and k = U NT (only when n = MAXL) by thread 0
-    auto put = [&](int k, double2 a0, double2 a1, double2 b0, double2 b1) {
-        const int kn = k ? N - k : 0;  // (n - k) mod n, k < n
-        // h_k = (c_k + conj c_{n-k}) / 2, h_{n-k} = conj h_k
-        const double2 ha = make_double2(0.5 * (a0.x + a1.x), 0.5 * (a0.y - a1.y));
-        const double2 hb = make_double2(0.5 * (b0.x + b1.x), 0.5 * (b0.y - b1.y));
-        // g = h_a + i h_b; the transform input is conj(g)
-        const double2 gk = make_double2(ha.x - hb.y, ha.y + hb.x);
-        const double2 gn = make_double2(ha.x + hb.y, -ha.y + hb.x);  // h_a* + i h_b* at n-k
-        buf[pd(k)] = input_point(conj2(gk), d, ch, k);
-        if (kn != k) buf[pd(kn)] = input_point(conj2(gn), d, ch, kn);
-    };
-    // the four folded bins of one k: c_a(k), c_a(n-k), c_b(k), c_b(n-k)
-    auto bins = [&](int k, double2 &a0, double2 &a1, double2 &b0, double2 &b1) {
-        const int kn = k ? N - k : 0;  // (n - k) mod n, k < n
-        if (lds_fold) {
-            const double2 *ta = buf + pd(L), *tb = buf + pd(L) + (mmax + 1);
-            a0 = fold_terms(ta, k, N, lim);
-            a1 = fold_terms(ta, kn, N, lim);
-            b0 = two ? fold_terms(tb, k, N, lim) : z;
-            b1 = two ? fold_terms(tb, kn, N, lim) : z;
-        } else {
-            // a0..b1 hold the first Delta of each bin (m = k, m = n-k) on entry
-            a0 = fold_bin(k <= mmax ? bin_term(a0, k, pha) : z, Da, dl.s_m, k, N, mmax, pha);
-            a1 = fold_bin(kn <= mmax ? bin_term(a1, kn, pha) : z, Da, dl.s_m, kn, N, mmax, pha);
-            b0 = two ? fold_bin(k <= mmax ? bin_term(b0, k, phb) : z, Db, dl.s_m, k, N, mmax, phb) : z;
-            b1 = two ? fold_bin(kn <= mmax ? bin_term(b1, kn, phb) : z, Db, dl.s_m, kn, N, mmax, phb) : z;
-        }
-    };
-    // bins k = threadIdx.x + u NT, u = 0 .. U (k = U NT only for thread 0 when
-    // n = MAXL); the second Delta of a bin pair (m = n - k) exists only for
-    // rings shorter than 2 mmax + 1, and aliases m + n <= mmax are loaded by
-    // the fold
+        // thread handles the bin pairs (k, n-k), k = threadIdx.x + u NT <= n/2:
+        // u < U for every thread, and k = U NT (only when n = MAXL) by thread 0
+        auto put = [&](int k, double2 a0, double2 a1, double2 b0, double2 b1) {
+            const int kn = k ? N - k : 0;  // (n - k) mod n, k < n
+            // h_k = (c_k + conj c_{n-k}) / 2, h_{n-k} = conj h_k
+            const double2 ha = make_double2(0.5 * (a0.x + a1.x), 0.5 * (a0.y - a1.y));
+            const double2 hb = make_double2(0.5 * (b0.x + b1.x), 0.5 * (b0.y - b1.y));
+            // g = h_a + i h_b; the transform input is conj(g)
+            const double2 gk = make_double2(ha.x - hb.y, ha.y + hb.x);
+            const double2 gn = make_double2(ha.x + hb.y, -ha.y + hb.x);  // h_a* + i h_b* at n-k
+            buf[lds_at(k, swz)] = input_point(conj2(gk), d, ch, k);
+            if (kn != k) buf[lds_at(kn, swz)] = input_point(conj2(gn), d, ch, kn);
+        };
+        // the four folded bins of one k: c_a(k), c_a(n-k), c_b(k), c_b(n-k)
+        auto bins = [&](int k, double2 &a0, double2 &a1, double2 &b0, double2 &b1) {
+            const int kn = k ? N - k : 0;  // (n - k) mod n, k < n
+            if (lds_fold) {
+                a0 = fold_terms(ta, k, N, lim);
+                a1 = fold_terms(ta, kn, N, lim);
+                b0 = two ? fold_terms(tb, k, N, lim) : z;
+                b1 = two ? fold_terms(tb, kn, N, lim) : z;
+            } else {
+                // a0..b1 hold the first Delta of each bin (m = k, m = n-k) on entry
+                a0 = fold_bin(k <= mmax ? bin_term(a0, k, pha) : z, Da, dl.s_m, k, N, mmax, pha);
+                a1 = fold_bin(kn <= mmax ? bin_term(a1, kn, pha) : z, Da, dl.s_m, kn, N, mmax, pha);
+                b0 = two ? fold_bin(k <= mmax ? bin_term(b0, k, phb) : z, Db, dl.s_m, k, N, mmax, phb) : z;
+                b1 = two ? fold_bin(kn <= mmax ? bin_term(b1, kn, phb) : z, Db, dl.s_m, kn, N, mmax, phb) : z;
+            }
+        };
+        // bins k = threadIdx.x + u NT, u = 0 .. U (k = U NT only for thread 0 when
+        // n = MAXL); the second Delta of a bin pair (m = n - k) exists only for
+        // rings shorter than 2 mmax + 1, and aliases m + n <= mmax are loaded by
+        // the fold
 #pragma unroll
-    for (int u = 0; u <= U; ++u) {
-        const int k = threadIdx.x + u * NT;
-        const int kn = k ? N - k : 0;  // (n - k) mod n, k < n
-        const bool ok = !lds_fold && 2 * k <= N && kn <= mmax;
-        double2 a0 = fa[u], b0 = fb[u];
-        double2 a1 = ok ? Da[kn * dl.s_m] : z;
-        double2 b1 = (ok && two) ? Db[kn * dl.s_m] : z;
-        if (2 * k <= N) {
-            bins(k, a0, a1, b0, b1);
-            put(k, a0, a1, b0, b1);
+        for (int u = 0; u <= U; ++u) {
+            const int k = threadIdx.x + u * NT;
+            const int kn = k ? N - k : 0;  // (n - k) mod n, k < n
+            const bool ok = !lds_fold && 2 * k <= N && kn <= mmax;
+            double2 a0 = fa[u], b0 = fb[u];
+            double2 a1 = ok ? Da[kn * dl.s_m] : z;
+            double2 b1 = (ok && two) ? Db[kn * dl.s_m] : z;
+            if (2 * k <= N) {
+                bins(k, a0, a1, b0, b1);
+                put(k, a0, a1, b0, b1);
+            }
         }
     }
     __syncthreads();
@@ -824,11 +1060,23 @@ __global__ __launch_bounds__(NT, 4) void k_fft_syn(RingPlan one, const RingPlan 
     double *outb = P.mout + (int64_t)js.mb * P.npix + P.ofs[js.rb];
     // the last stage writes the pixels when it can (radix 4 or 8)
     const bool reg_out = reg_last(d);
-    transform<MAXL, NT, LdsIn, PixelsOut>(buf, d, TwLds{tlo, thi}, LdsIn{buf}, false,
-                                          PixelsOut{outa, outb, two}, true);
+    if (swz)
+        transform_pow2<MAXL, NT, LdsIn, PixelsOut>(buf, d, TwLds{tlo, thi}, LdsIn{buf}, PixelsOut{outa, outb, two});
+    else
+        transform<MAXL, NT, LdsIn, PixelsOut>(buf, d, TwLds{tlo, thi}, LdsIn{buf}, false,
+                                              PixelsOut{outa, outb, two}, true);
     if (reg_out) return;
+    if (half) {
+#pragma unroll 1
+        for (int t = threadIdx.x; t < N; t += NT) {
+            const double2 v = result_at(buf, d, ch, t, swz);
+            outa[2 * t] = v.x;
+            outa[2 * t + 1] = -v.y;
+        }
+        return;
+    }
     for (int j = threadIdx.x; j < N; j += NT) {
-        const double2 z = result_at(buf, d, ch, j);  // FFT(conj g)_j; IDFT(g)_j = conj of it
+        const double2 z = result_at(buf, d, ch, j, swz);  // FFT(conj g)_j; IDFT(g)_j = conj of it
         outa[j] = z.x;
         if (two) outb[j] = -z.y;
     }
@@ -848,7 +1096,9 @@ __global__ __launch_bounds__(NT, 4) void k_fft_ana(RingPlan one, const RingPlan 
     const bool two = js.two;
     const DescP d = ro(P.descs) + P.ring_desc[js.ra];
     const int N = d->n;
+    const int swz = d->L == MAXL ? 15 : 0;  // points of LDS swizzled
     load_twiddles<NT>(tlo, thi, d->tw, d->L);
+    const bool half = d->half != 0;  // one sequence of 2 N pixels
     Chirp ch{clo, chi, N, 0.0};
     if (d->bluestein) {
         ch = load_chirp<NT>(clo, chi, N);
@@ -856,13 +1106,15 @@ __global__ __launch_bounds__(NT, 4) void k_fft_ana(RingPlan one, const RingPlan 
     }
     const double pa = P.phi0[js.ra], wa = P.weight[js.ra];
     const double pb = P.phi0[js.rb], wb = P.weight[js.rb];
+    // one phase for both sequences and no m beyond a turn of the ring
+    const bool plain = !half && N > mmax && pa == pb && (P.ph_tab || pa == 0.0);
     // phase tables: visible after the barrier that follows the input below
     Phase pha{nullptr, nullptr, pa}, phb{nullptr, nullptr, pb};
-    if (P.ph_tab) {
-        double2 *tab = buf + padded_len<MAXL>();
+    if (P.ph_tab && !(plain && pa == 0.0)) {
+        double2 *tab = buf + MAXL;
         pha = load_phases<NT>(tab, mmax, pa);
         phb = pha;
-        if (two && js.rb != js.ra) phb = load_phases<NT>(tab + kPhLo + phase_hi_entries(mmax), mmax, pb);
+        if (two && js.rb != js.ra && pa != pb) phb = load_phases<NT>(tab + kPhLo + phase_hi_entries(mmax), mmax, pb);
     }
     const double *ina = P.min + (int64_t)js.ma * P.npix + P.ofs[js.ra];
     const double *inb = P.min + (int64_t)js.mb * P.npix + P.ofs[js.rb];
@@ -875,22 +1127,53 @@ __global__ __launch_bounds__(NT, 4) void k_fft_ana(RingPlan one, const RingPlan 
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int j = threadIdx.x + u * NT;
-            va[u] = j < N ? ina[j] : 0.0;
-            vb[u] = (two && j < N) ? inb[j] : 0.0;
+            va[u] = j < N ? ina[half ? 2 * j : j] : 0.0;
+            vb[u] = j < N && (two || half) ? (half ? ina[2 * j + 1] : inb[j]) : 0.0;
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int j = threadIdx.x + u * NT;
-            if (j < N) buf[pd(j)] = input_point(make_double2(va[u], vb[u]), d, ch, j);
+            if (j < N) buf[lds_at(j, swz)] = input_point(make_double2(va[u], vb[u]), d, ch, j);
         }
     }
     __syncthreads();  // twiddle and phase tables (and the points) visible
-    transform<MAXL, NT, PixelsIn>(buf, d, TwLds{tlo, thi}, PixelsIn{ina, inb, two}, true);
+    if (swz)
+        transform_pow2<MAXL, NT, PixelsIn>(buf, d, TwLds{tlo, thi}, PixelsIn{ina, inb, two});
+    else
+        transform<MAXL, NT, PixelsIn>(buf, d, TwLds{tlo, thi}, PixelsIn{ina, inb, two}, true);
     double2 *Da = P.dout + js.ma * dl.s_map + js.ra * dl.s_ring;
     double2 *Db = P.dout + js.mb * dl.s_map + js.rb * dl.s_ring;
+    if (half) {
+        half_terms<NT>(Da, dl.s_m, mmax, wa, d, ch, pha, buf);
+        return;
+    }
+    if (plain) {
+        auto terms = [&](auto turn) {
+            constexpr bool TURN = decltype(turn)::value;
+#pragma unroll 2
+            for (int m = threadIdx.x; m <= mmax; m += NT) {
+                const int kn = m ? N - m : 0;
+                const double2 Z = result_at(buf, d, ch, m, swz), Zn = result_at(buf, d, ch, kn, swz);
+                double2 Sa = make_double2(0.5 * (Z.x + Zn.x), 0.5 * (Z.y - Zn.y));
+                double2 Sb = make_double2(0.5 * (Z.y + Zn.y), -0.5 * (Z.x - Zn.x));
+                if constexpr (TURN) {
+                    const double2 e = conj2(pha(m));
+                    Sa = cmul(Sa, e);
+                    Sb = cmul(Sb, e);
+                }
+                Da[m * dl.s_m] = make_double2(wa * Sa.x, wa * Sa.y);
+                if (two) Db[m * dl.s_m] = make_double2(wb * Sb.x, wb * Sb.y);
+            }
+        };
+        if (pa != 0.0)
+            terms(std::true_type{});
+        else
+            terms(std::false_type{});
+        return;
+    }
     for (int m = threadIdx.x; m <= mmax; m += NT) {
         const int k = m < N ? m : m % N, kn = k ? N - k : 0;  // m mod n, (n - k) mod n
-        const double2 Z = result_at(buf, d, ch, k), Zn = result_at(buf, d, ch, kn);
+        const double2 Z = result_at(buf, d, ch, k, swz), Zn = result_at(buf, d, ch, kn, swz);
         // S_a = (Z_k + conj Z_{n-k}) / 2, S_b = (Z_k - conj Z_{n-k}) / (2i)
         const double2 Sa = make_double2(0.5 * (Z.x + Zn.x), 0.5 * (Z.y - Zn.y));
         const double2 Sb = make_double2(0.5 * (Z.y + Zn.y), -0.5 * (Z.x - Zn.x));
@@ -941,7 +1224,7 @@ int set_lds_attr() {
     return SHT_OK;
 }
 
-static_assert((tw_entries<kMaxFftLen>() + chirp_entries<kMaxFftLen>() + padded_len<kMaxFftLen>()) * sizeof(double2) <= kMaxLds,
+static_assert((tw_entries<kMaxFftLen>() + chirp_entries<kMaxFftLen>() + kMaxFftLen) * sizeof(double2) <= kMaxLds,
               "largest class fits LDS");
 
 // the phase tables of a job's two rings; used for mmax < 64 kPhHiMax when
@@ -951,14 +1234,11 @@ int phase_tables_fit(int mmax, size_t lds) {
     return phase_hi_entries(mmax) <= kPhHiMax && lds + phase_table_bytes(mmax) <= (size_t)kMaxLds;
 }
 
-// LDS bytes and layout flags of class MAXL for a plan of this mmax
+// LDS bytes and layout flag of class MAXL for a plan of this mmax
 template <int MAXL>
-size_t class_lds(int mmax, bool synthesis, int *fold_rows, int *ph_tab) {
-    const size_t base = (size_t)(tw_entries<MAXL>() + chirp_entries<MAXL>() + padded_len<MAXL>()) * sizeof(double2);
-    const size_t rows = 2 * (size_t)(mmax + 1) * sizeof(double2);
-    // the small-length class of synthesis keeps the phased terms in LDS when they fit
-    *fold_rows = (synthesis && MAXL <= 1024 && base + rows <= kMaxLds) ? 1 : 0;
-    size_t lds = base + (*fold_rows ? rows : 0);
+size_t class_lds(int mmax, bool synthesis, int *ph_tab) {
+    size_t lds = (size_t)(tw_entries<MAXL>() + chirp_entries<MAXL>() + MAXL) * sizeof(double2);
+    if (synthesis && kColumns<MAXL>) lds += 2 * fft_threads<MAXL>() * sizeof(double2);
     *ph_tab = phase_tables_fit(mmax, lds);
     if (*ph_tab) lds += phase_table_bytes(mmax);
     return lds;
@@ -1013,10 +1293,10 @@ RingPlan ring_plan(const GeomPlan &p, int c, int mmax, int nmaps, DeltaLayout dl
     P.weight = p.weight;
     P.ofs = p.ofs;
     switch (c) {
-        case 0: *lds = class_lds<1024>(mmax, synthesis, &P.fold_rows, &P.ph_tab); break;
-        case 1: *lds = class_lds<2048>(mmax, synthesis, &P.fold_rows, &P.ph_tab); break;
-        case 2: *lds = class_lds<4096>(mmax, synthesis, &P.fold_rows, &P.ph_tab); break;
-        default: *lds = class_lds<8192>(mmax, synthesis, &P.fold_rows, &P.ph_tab); break;
+        case 0: *lds = class_lds<1024>(mmax, synthesis, &P.ph_tab); break;
+        case 1: *lds = class_lds<2048>(mmax, synthesis, &P.ph_tab); break;
+        case 2: *lds = class_lds<4096>(mmax, synthesis, &P.ph_tab); break;
+        default: *lds = class_lds<8192>(mmax, synthesis, &P.ph_tab); break;
     }
     return P;
 }

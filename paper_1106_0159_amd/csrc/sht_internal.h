@@ -123,15 +123,18 @@ struct CoefTables : Fenced {
 // One FFT length (device view).  Points of length n are transformed in LDS
 // either directly (L == n, radices of n) or by Bluestein's chirp-z method
 // with the shortest 5-smooth length L >= 2n - 2.
+// second entry of the job of a ring transformed by itself (FftDesc::half); -1: no second ring
+constexpr int kHalfJob = -2;
 struct FftDesc {
-    int n;
+    int n;                 // points of the transform (half the ring's when half)
     int L;
     int nrad;
     int bluestein;
+    int half;              // one ring of 2n points at a time, its pixel pairs as complex points (Bluestein)
     int rad[kMaxRadices];
     const double2 *tw;     // W_L[t] = exp(-2 pi i t / L), t < L
     const double2 *kern;   // Bluestein: FFT_L of the extended chirp b_t = exp(i pi t^2 / n)
-                           // (b_{L-t} = b_t, zero between), divided by L
+                           // (b_{L-t} = b_t, zero between), divided by L; entries 0 .. L/2 of an even sequence
 };
 
 // Where each (m, slot) recurrence starts, for one coefficient set on one
@@ -230,13 +233,13 @@ inline DeltaLayout alm2map_layout(int nrings, int mmax, int nmaps, uint32_t flag
 // One length class of one plan's ring stage as the ring kernels read it: a
 // kernel argument for a single call, or an entry of a batch's device table
 // (the jobs of every request and class in one launch per class).  Ring-major
-// Delta unless dl.map_minor; nmaps maps per job (1 in batches).  fold_rows
-// and ph_tab: the LDS layout of this entry (rows of phased terms, phase tables).
+// Delta unless dl.map_minor; nmaps maps per job (1 in batches).  ph_tab:
+// this entry keeps phase tables in LDS.
 struct RingPlan {
-    int mmax, nmaps, njobs, fold_rows, ph_tab;
+    int mmax, nmaps, njobs, ph_tab;
     int64_t npix;
     DeltaLayout dl;
-    const int2 *jobs;          // [njobs] (ring a, ring b or -1) of this class
+    const int2 *jobs;          // [njobs] (ring a, ring b, -1 or kHalfJob) of this class
     const int32_t *ring_desc;  // [nrings] index into descs
     const FftDesc *descs;
     const double *phi0, *weight;

@@ -433,11 +433,16 @@ static bool factor_all(int n, std::vector<int> &rad) {
     return (int)rad.size() <= kMaxRadices;
 }
 
-// Cost of a prime-radix stage in flops per point and unit of R, against 400
-// per point of Bluestein's length: of the weights 12, 6, 4 and 3 the last
-// timed best with the mirror-paired stage (ring stages at HEALPix 1024,
-// one map and 64 maps).
-constexpr double kPrimeCost = 3.0;
+// Which transform a length takes that is not 5-smooth, in one unit of time per
+// ring pair (256 rings of one length, 16 maps, both directions; measured
+// 0.22 ns per unit): direct R-term stages n (kBaseCost + sum of the primes);
+// Bluestein of both rings on L points kPairCost L; of each ring by itself as
+// n / 2 complex points, kHalfCost L.  Figures behind it (us, synthesis, 16
+// maps and one map): n = 2848 = 32 x 89 direct 116 and 25, halves 167 and 23;
+// 3084 = 12 x 257 237 and 48 against 171 and 22; 5908 = 28 x 211 474 and 59
+// against 464 and 39; 8156 = 4 x 2039 3597 and 410 against 491 and 39; the
+// pair on 4096 points 109 and 22 (n = 2036), the halves on 2048 117 and 18.
+constexpr double kBaseCost = 90.0, kPairCost = 118.0, kHalfCost = 200.0;
 
 static bool smooth5(int n) {
     for (int p : {2, 3, 5})
@@ -445,30 +450,30 @@ static bool smooth5(int n) {
     return n == 1;
 }
 
-// Forward DFT (sign -1) of a 5-smooth length in long double, by recursive
-// decimation in time over the factors 2, 3, 5.
-static void host_fft_smooth(std::vector<cld> &a) {
-    const size_t n = a.size();
-    if (n == 1) return;
-    size_t p = (n % 2 == 0) ? 2 : (n % 3 == 0) ? 3 : 5;
-    const size_t m = n / p;
-    std::vector<std::vector<cld>> sub(p, std::vector<cld>(m));
-    for (size_t j = 0; j < m; ++j)
-        for (size_t r = 0; r < p; ++r) sub[r][j] = a[j * p + r];
-    for (auto &v : sub) host_fft_smooth(v);
-    for (size_t k = 0; k < n; ++k) {
-        cld acc(0, 0);
-        for (size_t r = 0; r < p; ++r) {
-            const long double ang = -2.0L * kPiL * (long double)((r * k) % n) / (long double)n;
-            acc += sub[r][k % m] * cld(cosl(ang), sinl(ang));
-        }
-        a[k] = acc;
+// Forward DFT (sign -1) of a power-of-two length in long double, in place, w
+// the roots exp(-2 pi i t / L), t < L / 2: radix 2 on bit-reversed points.
+static void host_fft_pow2(std::vector<cld> &a, const std::vector<cld> &w) {
+    const size_t L = a.size();
+    for (size_t i = 1, j = 0; i < L; ++i) {
+        size_t bit = L >> 1;
+        for (; j & bit; bit >>= 1) j ^= bit;
+        j ^= bit;
+        if (i < j) std::swap(a[i], a[j]);
     }
+    for (size_t h = 1; h < L; h *= 2)
+        for (size_t o = 0; o < L; o += 2 * h)
+            for (size_t k = 0; k < h; ++k) {
+                const cld t = w[k * (L / (2 * h))], x = a[o + k + h];
+                const cld v(x.real() * t.real() - x.imag() * t.imag(), x.real() * t.imag() + x.imag() * t.real());
+                a[o + k + h] = a[o + k] - v;
+                a[o + k] += v;
+            }
 }
 
 struct FftCache {
     std::map<int, double2 *> twiddles;      // by L
     std::map<int, FftDesc> descs;           // by n
+    std::map<int, std::vector<cld>> roots;  // by L, for host_fft_pow2
     std::vector<void *> owned;
 };
 static auto &g_fft = *new std::map<int, std::unique_ptr<FftCache>>();  // by device
@@ -523,57 +528,73 @@ static int fft_desc(FftCache &fc, int n, FftDesc *out, FftAdded &added) {
     d.n = n;
     std::vector<int> rad;
     int rc;
-    // Direct transform of length n when it is 5-smooth, or when its direct
-    // R-term stages (with the mirror-paired inputs about kPrimeCost R flops
-    // per point each) cost less than Bluestein's two transforms of length L
-    // (taken as 400 flops per point of L), or when Bluestein's L would not
-    // fit the largest class.
+    if (n > kMaxFftLen) return SHT_EUNSUPPORTED;
+    // Direct when 5-smooth; otherwise the cheapest of what fits (costs above).
     // Bluestein's cyclic convolution takes the chirp at offsets -(n-1) ..
     // n-1.  The chirp is even in its offset, so the one pair of offsets that
     // share an index modulo L = 2n - 2, +-(n-1), needs the same value there:
-    // L >= 2n - 2 is exact (L = 4096 for n = 2049 = 2 lmax + 1 at lmax 1024,
-    // where L >= 2n - 1 would take 4320 and the 8192 class).
-    int Lb = n > 1 ? 2 * n - 2 : 1;
-    while (!smooth5(Lb)) ++Lb;
-    std::vector<int> all;
-    const bool all_ok = factor_all(n, all);
-    double direct = 0.0;
-    for (int f : all) direct += f > 5 ? kPrimeCost * f * n : 0.0;
+    // L >= 2n - 2 is exact (L = 4096 for n = 2049 = 2 lmax + 1 at lmax 1024).
+    // L is the length of a class, whose transform is the fastest.
+    const int kNone = 0;
+    auto class_len = [&](int need) {
+        for (int L : kFftClassLen)
+            if (L >= need) return L;
+        return kNone;
+    };
     if (factor_small(n, rad)) {
         d.L = n;
-        d.bluestein = 0;
-    } else if (all_ok && (Lb > kMaxFftLen || direct <= 400.0 * Lb)) {
-        rad = all;
-        d.L = n;
-        d.bluestein = 0;
     } else {
-        const int L = Lb;
-        d.L = L;
-        d.bluestein = 1;
+        const int Lpair = class_len(2 * n - 2), Lhalf = n % 2 == 0 ? class_len(n - 2) : kNone;
+        const double pair = Lpair ? kPairCost * Lpair : HUGE_VAL, half = Lhalf ? kHalfCost * Lhalf : HUGE_VAL;
+        double direct = kBaseCost * n;
+        if (factor_all(n, rad)) {
+            for (int f : rad) direct += f > 5 ? (double)f * n : 0.0;
+        } else {
+            direct = HUGE_VAL;
+        }
+        if (direct <= std::min(pair, half)) {
+            if (direct == HUGE_VAL) return SHT_EUNSUPPORTED;
+            d.L = n;
+        } else {
+            d.bluestein = 1;
+            d.half = half < pair;
+            if (d.half) d.n = n / 2;
+            d.L = d.half ? Lhalf : Lpair;
+        }
+    }
+    if (d.bluestein) {
+        const int L = d.L, nb = d.n;
         factor_small(L, rad);
+        std::vector<cld> &w = fc.roots[L];
+        if (w.empty()) {
+            w.resize(L / 2);
+            for (int t = 0; t < L / 2; ++t) {
+                const long double a = -2.0L * kPiL * (long double)t / (long double)L;
+                w[t] = cld(cosl(a), sinl(a));
+            }
+        }
         // chirp b_t = exp(i pi t^2 / n), angle reduced exactly: t^2 mod 2n
         // (the kernels compute b_t themselves; the plan keeps the spectrum of
         // its extension to length L: b at t and at L - t, which are one index
-        // for t = n - 1 when L = 2n - 2, with the same value)
+        // for t = n - 1 when L = 2n - 2, with the same value).  The spectrum is
+        // even: entries 0 .. L/2.
         std::vector<cld> ext(L, cld(0, 0));
-        for (int t = 0; t < n; ++t) {
-            const long long q = (long long)t * t % (2LL * n);
-            const long double a = kPiL * (long double)q / (long double)n;
+        for (int t = 0; t < nb; ++t) {
+            const long long q = (long long)t * t % (2LL * nb);
+            const long double a = kPiL * (long double)q / (long double)nb;
             const cld v(cosl(a), sinl(a));
             ext[t] = v;
             if (t > 0) ext[L - t] = v;
         }
-        host_fft_smooth(ext);
-        std::vector<double2> k(L);
-        for (int t = 0; t < L; ++t)
-            k[t] = make_double2((double)(ext[t].real() / L), (double)(ext[t].imag() / L));
+        host_fft_pow2(ext, w);
+        std::vector<double2> k(L / 2 + 1);
+        for (int t = 0; t <= L / 2; ++t) k[t] = make_double2((double)(ext[t].real() / L), (double)(ext[t].imag() / L));
         double2 *dk = nullptr;
         rc = upload(k, &dk, fc.owned);
         if (dk) added.ptrs.push_back(dk);
         if (rc) return rc;
         d.kern = dk;
     }
-    if (d.L > kMaxFftLen) return SHT_EUNSUPPORTED;
     // Stockham stages may come in any order: with two radix-8/4 factors or
     // more, one of them goes last, so that both the first and the last stage
     // can move their points through registers (pixels in, pixels out)
@@ -809,7 +830,12 @@ static int build_geom(int dev, const HostGeom &hg, std::shared_ptr<GeomPlan> *ou
         const int L = descs[ring_desc[j.x]].L;
         int c = 0;
         while (c < kFftClasses - 1 && L > kFftClassLen[c]) ++c;
-        cls[c].push_back(j);
+        if (descs[ring_desc[j.x]].half) {
+            cls[c].push_back(make_int2(j.x, kHalfJob));
+            if (j.y >= 0) cls[c].push_back(make_int2(j.y, kHalfJob));
+        } else {
+            cls[c].push_back(j);
+        }
     }
     for (int c = 0; c < kFftClasses; ++c) {
         p.class_count[c] = (int)cls[c].size();
