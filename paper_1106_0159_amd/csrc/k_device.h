@@ -13,9 +13,18 @@ namespace sht {
 // tiles or groups) of one m share one XCD's L2 for its coefficient column,
 // the 8 consecutive m whose entries fill one 128-byte line of a Delta row are
 // written (read) through the same L2, m still ascends in launch order, and
-// the snake order keeps the XCDs' shares of the work equal.
+// the snake order keeps the XCDs' shares of the work equal.  Within an XCD the
+// dispatcher deals workgroups to its 4 shader engines in turn and waits for the
+// one whose turn it is: with an even number of parts each engine would get the
+// same parts of every m, the short polar tiles or the long equatorial ones, and
+// the first would idle (a fifth of the CU time at 4 tiles), so the parts of
+// successive m start one further on.  Synthesis at HEALPix 2048 / lmax 4096 (4
+// tiles) 3.05 -> 2.60 ms, 1024 / 2048 (2 tiles) 424 -> 408 us; analysis at 2048
+// / 4096 (2 groups) 4.97 -> 4.21 ms with the ring stage.  A grid that is all resident at
+// once waits for nothing and keeps the plain order (HEALPix 347: 85 us, turned 88).
 constexpr int kXcds = 8;
 constexpr int kMBlock = 8;  // m values per 128-byte line of a Delta row
+constexpr unsigned kTurnMin = 2048;  // workgroups, 8 per CU
 struct MPart {
     int m, part;
 };
@@ -24,7 +33,9 @@ __device__ __forceinline__ MPart xcd_m_part(int parts) {
     const int per = kMBlock * parts;
     const int j = k / per, rem = k - j * per;
     const int xs = (j & 1) ? kXcds - 1 - x : x;
-    return {(j * kXcds + xs) * kMBlock + rem / parts, rem % parts};
+    const int r = rem / parts;
+    const int turn = parts % 2 || gridDim.x < kTurnMin ? 0 : parts == 2 ? r / 2 : r;
+    return {(j * kXcds + xs) * kMBlock + r, (rem + turn) % parts};
 }
 
 // number of m values launched: mmax + 1 rounded up to a multiple of kMBlock * kXcds
