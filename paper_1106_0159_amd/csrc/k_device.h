@@ -45,6 +45,17 @@ inline int64_t padded_m(int mmax) {
 }
 inline bool grid_ok(int64_t n) { return n > 0 && n < (int64_t)INT32_MAX; }
 
+// One load from each of the first 128-byte lines, one per thread, of p[stride * i],
+// i0 <= i <= i1 (addresses clamped to i1, so every load is in bounds).  The
+// workgroup's pass over a coefficient column brings it into this XCD's L2
+// ahead of the wave-uniform loads that use it; the value is only handed to an
+// empty asm at the end of the kernel, so nothing waits for it before then.
+__device__ __forceinline__ double warm_l2(const double *p, int stride, int i0, int i1) {
+    const int per_line = 16 / stride;  // entries per 128 bytes
+    const int i = min(i0 + per_line * (int)threadIdx.x, i1);
+    return p[(int64_t)stride * i];
+}
+
 // Wave-wide min / max, returned as a wave-uniform (scalar) value so that
 // loops bounded by it stay uniform and their coefficient loads scalar.  Lane
 // exchanges in registers (DPP within a row of 16, then the permlane swaps):

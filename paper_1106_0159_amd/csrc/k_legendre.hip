@@ -196,17 +196,6 @@ __device__ __forceinline__ void finish_column(int lmax, int m, ParityFac f, Sum 
     }
 }
 
-// One load from each of the first kBlock 128-byte lines of p[stride * i],
-// i0 <= i <= i1 (addresses clamped to i1, so every load is in bounds).  The
-// workgroup's pass over a coefficient column brings it into this XCD's L2
-// ahead of the wave-uniform loads that use it; the value is only handed to an
-// empty asm at the end of the kernel, so nothing waits for it before then.
-__device__ __forceinline__ double warm_l2(const double *p, int stride, int i0, int i1) {
-    const int per_line = 16 / stride;  // entries per 128 bytes
-    const int i = min(i0 + per_line * (int)threadIdx.x, i1);
-    return p[(int64_t)stride * i];
-}
-
 // Synthesis of one m of M maps over a tile of slots: a wave (li / 64 of the
 // threads sharing the tile) owns 64 T consecutive slots, its lanes the slots
 // 64 u + lane of them, u < T (so that a set of 64 that has not started is

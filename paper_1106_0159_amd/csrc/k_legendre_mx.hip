@@ -190,6 +190,8 @@ __global__ __launch_bounds__(kBlock, 2) void k_leg_syn_mx(int lmax, int mmax, in
     const int m = mp.m, tile = mp.part;
     if (m > mmax) return;  // padding of the m range
     const int cg = blockIdx.y;
+    const int64_t base = uniform64((int64_t)m * (2 * lmax + 1 - m) / 2);  // (l, m) lives at base + l
+    const double warm_al = warm_l2(alpha + base, 1, m, lmax);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int c16 = lane & 15, kq = lane >> 4;
     const int slot = tile * kBlock + (int)threadIdx.x;
@@ -201,7 +203,6 @@ __global__ __launch_bounds__(kBlock, 2) void k_leg_syn_mx(int lmax, int mmax, in
     const int lo = wave_min(ls);
     const int hi = wave_max(ls <= lmax ? ls : m);
 
-    const int64_t base = uniform64((int64_t)m * (2 * lmax + 1 - m) / 2);  // (l, m) lives at base + l
     const double *__restrict__ al = alpha + base;
     const int64_t apm = ((int64_t)cg * mxblocks + mxofs[m]) * kTile;  // this m's tiles (elements)
     const int nb = mx_blocks(lmax, m);
@@ -230,6 +231,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_leg_syn_mx(int lmax, int mmax, in
                     for (int r = 0; r < 4; ++r) dsum[p][rf][cf][r] = 0.0;
     }
 
+    asm volatile("" ::"v"(warm_al));
     double q1 = 0.0, q2 = 0.0;  // a pair carries zeros until it starts
     const int kb0 = lo <= lmax ? (lo - m) / kMxL : nb;
     // a' operands: FP32 one block ahead, those of block kb loaded while block
@@ -459,6 +461,8 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void k_leg_ana_mx(i
     // sorted by latitude and start late near the poles, so every wave gets
     // tiles from the whole range and the waves' work per block stays even
     auto tile0 = [&](int t) { return grp * kGroup + (t * WAVES + w) * 64; };
+    const int64_t base = uniform64((int64_t)m * (2 * lmax + 1 - m) / 2);  // (l, m) lives at base + l
+    const double warm_al = warm_l2(alpha + base, 1, m, lmax);
 
     double x[kAnaMxTiles], q1[kAnaMxTiles], q2[kAnaMxTiles];
     double2 stv[kAnaMxTiles];
@@ -503,7 +507,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void k_leg_ana_mx(i
     for (int i = 0; i < WAVES; ++i) lo = min(lo, wlo[i]);
     lo = __builtin_amdgcn_readfirstlane(lo);
 
-    const int64_t base = uniform64((int64_t)m * (2 * lmax + 1 - m) / 2);  // (l, m) lives at base + l
+    asm volatile("" ::"v"(warm_al));
     const double *__restrict__ al = alpha + base;
     const int nb = mx_blocks(lmax, m);
     const int kb0 = lo <= lmax ? (lo - m) / kMxL : nb;
@@ -584,25 +588,36 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void k_leg_ana_mx(i
             for (int p = 0; p < 2; ++p)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) red[buf][b][w][p][4 * kq + r][c16] = acc2[b][p][r];
+        // element e of the pair: block, parity, k and map; c_lm loaded ahead of the barrier
+        constexpr int kPer = (kAnaMxOut + kThreads - 1) / kThreads;
+        auto l_of = [&](int e) {
+            const int b = e / (2 * kMxHalf * kAnaMxMaps), p = (e / (kMxHalf * kAnaMxMaps)) % 2, k = (e / kAnaMxMaps) % kMxHalf;
+            return m + kMxL * (kb - slot + b) + 2 * k + p;
+        };
+        double cf[kPer];
+        if (groups == 1) {
+#pragma unroll
+            for (int i = 0; i < kPer; ++i) cf[i] = cfac[base + min(l_of(threadIdx.x + i * kThreads), lmax)];
+        }
         __syncthreads();
-        for (int e = threadIdx.x; e < kAnaMxOut; e += kThreads) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int e = threadIdx.x + i * kThreads;
             const int b = e / (2 * kMxHalf * kAnaMxMaps);
             const int p = (e / (kMxHalf * kAnaMxMaps)) % 2;
             const int k = (e / kAnaMxMaps) % kMxHalf, mm = e % kAnaMxMaps;
-            const int l = m + kMxL * (kb - slot + b) + 2 * k + p, map = cg * kAnaMxMaps + mm;
-            if (b <= slot && l <= lmax && map < nmaps) {
+            const int l = l_of(e), map = cg * kAnaMxMaps + mm;
+            if (e < kAnaMxOut && b <= slot && l <= lmax && map < nmaps) {
                 double sr = 0.0, si = 0.0;
 #pragma unroll
                 for (int v = 0; v < WAVES; ++v) {
                     sr += red[buf][b][v][p][k][2 * mm];
                     si += red[buf][b][v][p][k][2 * mm + 1];
                 }
-                if (groups == 1) {
-                    const double c = cfac[base + l];
-                    *out_at(map, l) = make_double2(sr * c, m == 0 ? 0.0 : si * c);
-                } else {
+                if (groups == 1)
+                    *out_at(map, l) = make_double2(sr * cf[i], m == 0 ? 0.0 : si * cf[i]);
+                else
                     *out_at(map, l) = make_double2(sr, si);  // scaled and Im a_l0 cleared by k_ana_combine
-                }
             }
         }
 #pragma unroll
