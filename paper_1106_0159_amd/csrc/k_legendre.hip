@@ -771,7 +771,7 @@ __device__ __forceinline__ void ana_wave(const AnaArgs &A, int m, int map, SumRo
     double2 fac = factors(lo);
     auto one = [&](int j0, auto full) {
         cp.load(nxt);
-        const double2 fac_next = factors(j0 + kChunk);
+        double2 fac_next = factors(j0 + kChunk);
         double acc[kVals];
         S.template chunk<decltype(full)::value, kPolarSlots / 64>(j0, nj - j0, cur, acc);
         // S_j of this lane's column and S_{j-1}: rows v and v - 4, the latter for
@@ -782,6 +782,9 @@ __device__ __forceinline__ void ana_wave(const AnaArgs &A, int m, int map, SumRo
         __builtin_amdgcn_wave_barrier();
         set ^= 1;
         cur = nxt;
+        // the next factors are waited for here: behind the store the wait would
+        // include the store's own way to memory, in every chunk
+        asm volatile("" : "+v"(fac_next.x), "+v"(fac_next.y));
         const int l = m + 2 * (j0 + (fv >> 2)) + (fc >> 1);
         if ((lane & 3) == 0 && l <= lmax) {
             const double r = fc < 2 ? fma(fac.x, v, fac.y * before) : fac.x * v;
