@@ -41,13 +41,14 @@
 // rings loop outermost; here a workgroup owns one m for a tile of ring
 // pairs, so the loop over l is uniform across a wave and a_lm, alpha are
 // wave-uniform scalar operands):
-//   synthesis  grid.x = (m, 1024-slot tile), m ascending (longest first),
-//              grid.y = map; four adjacent slots per lane, no reduction.
+//   synthesis  grid.x = (m, slot tile), m ascending (longest first), grid.y =
+//              map (or two maps); a wave owns 64 T slots, T per lane, no reduction.
 //   analysis   grid.x = (m, slot group), grid.y = map; a workgroup owns up
-//              to 256T slots of its m (T adjacent slots per lane); each wave
-//              sums its lanes through its own LDS rows, the four waves are
-//              added in wave order every 64 l, and groups are summed in
-//              order by a second small kernel: no atomics, deterministic.
+//              to 256 T slots of its m; each wave sums its lanes in registers
+//              and its own LDS rows, the four waves are added in wave order
+//              every 32 steps, and groups are summed in order by a second
+//              small kernel: no atomics, deterministic.  From three maps on the
+//              sums run on the matrix cores, four maps per workgroup.
 #include <type_traits>
 
 #include "k_device.h"
@@ -1225,7 +1226,7 @@ int launch_leg_syn(const CoefTables &c, const GeomPlan &p, const StartTable &s, 
     // (Powers of two only: a wave's slots must not straddle GeomPlan::npolar.)
     const int T = p.nslots <= kBlock ? 1 : p.nslots <= (nmaps >= 2 ? 2 : 3) * kBlock ? 2 : kSynSlotsPerLane;
     // several maps share each recurrence: 2 maps per workgroup (at 4 slots per
-    // lane faster than 4 maps and 2 slots: 29.7 against 30.6 ms for 64 maps at
+    // lane faster than 4 maps and 2 slots: with the one-step recurrence 29.7 against 30.6 ms for 64 maps at
     // HEALPix 1024 / lmax 2048)
     if (nmaps >= 2) {
         switch (T) {

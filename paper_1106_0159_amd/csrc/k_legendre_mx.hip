@@ -137,24 +137,41 @@ struct MxStart {
     int ls;
     double2 st;
 };
-__device__ __forceinline__ MxStart mx_start(int lmax, int m, int nslots, int slot, double x, ParityFac f,
-                                            const double *__restrict__ cfac, const int32_t *__restrict__ jstart,
-                                            const double2 *__restrict__ state) {
-    MxStart r{lmax + 1, make_double2(0.0, 0.0)};
-    if (slot >= nslots) return r;
-    const int j0 = jstart[(int64_t)m * nslots + slot];
-    if (j0 >= jcol_len(lmax, m)) return r;
-    const int64_t jb = jcol_base(lmax, m) + j0;
-    const double2 s = state[(int64_t)m * nslots + slot];
-    r.ls = m + 2 * j0;
-    if (j0 == 0) {
-        r.st.x = f.pe1[jb] * s.x;
-    } else {
-        const int64_t at = (int64_t)m * (2 * lmax + 1 - m) / 2 + r.ls;
-        r.st.y = x * f.po[jb - 1] * s.y / cfac[at - 1];
-        r.st.x = fma(f.pe1[jb - 1], s.y, f.pe2[jb - 2] * s.x) / cfac[at - 2];
+// T slots of a lane: one round of loads, and a second where the wave has a
+// start above l = m (no branch between the slots, so that they share it).
+template <int T>
+__device__ __forceinline__ void mx_starts(int lmax, int m, int nslots, const int (&slot)[T], const double (&x)[T],
+                                          ParityFac f, const double *__restrict__ cfac,
+                                          const int32_t *__restrict__ jstart, const double2 *__restrict__ state,
+                                          MxStart (&r)[T]) {
+    const int nj = jcol_len(lmax, m);
+    const int64_t jc = jcol_base(lmax, m), base = (int64_t)m * (2 * lmax + 1 - m) / 2;
+    int j0[T];
+    double2 s[T];
+    const double p0 = f.pe1[jc];
+    bool later = false;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const int64_t at = (int64_t)m * nslots + min(slot[t], nslots - 1);
+        j0[t] = jstart[at];
+        s[t] = state[at];
     }
-    return r;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const bool starts = slot[t] < nslots && j0[t] < nj;
+        r[t].ls = starts ? m + 2 * j0[t] : lmax + 1;
+        r[t].st = make_double2(starts ? p0 * s[t].x : 0.0, 0.0);
+        if (starts && j0[t] > 0) later = true;
+    }
+    if (!__ballot(later)) return;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const int k = max(min(j0[t], nj) - 1, 0), l = min(m + 2 * k + 1, lmax);
+        const double po = f.po[jc + k], pe1 = f.pe1[jc + k], pe2 = f.pe2[jc + max(k - 1, 0)];
+        const double c1 = cfac[base + l], c2 = cfac[base + m + 2 * k];
+        if (r[t].ls <= lmax && j0[t] > 0)
+            r[t].st = make_double2(fma(pe1, s[t].y, pe2 * s[t].x) / c2, x[t] * po * s[t].y / c1);
+    }
 }
 
 // LDS q tiles of one workgroup: per wave, parity and lane row, the four
@@ -197,9 +214,10 @@ __global__ __launch_bounds__(kBlock, 2) void k_leg_syn_mx(int lmax, int mmax, in
     const int slot = tile * kBlock + (int)threadIdx.x;
     const bool act = slot < nslots;
     const double x = act ? sx[slot] : 0.0;
-    const MxStart start = mx_start(lmax, m, nslots, slot, x, fac, cfac, jstart, state);
-    const int ls = start.ls;
-    const double2 stv = start.st;
+    MxStart start[1];
+    mx_starts<1>(lmax, m, nslots, {slot}, {x}, fac, cfac, jstart, state, start);
+    const int ls = start[0].ls;
+    const double2 stv = start[0].st;
     const int lo = wave_min(ls);
     const int hi = wave_max(ls <= lmax ? ls : m);
 
@@ -470,16 +488,22 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void k_leg_ana_mx(i
     float dp[kAnaMxTiles][16], dm[kAnaMxTiles][16];
     const double *__restrict__ dcol = reinterpret_cast<const double *>(delta) +
                                       2 * ((col_ok ? map_c : 0) * dl.s_map + m * dl.s_m) + (c16 & 1);
-    int mylo = lmax + 1;
+    int mylo = lmax + 1, slot_of[kAnaMxTiles];
+    MxStart start[kAnaMxTiles];
 #pragma unroll
     for (int t = 0; t < kAnaMxTiles; ++t) {
-        const int slot = tile0(t) + lane;
-        const bool act = slot < nslots;
-        x[t] = act ? sx[slot] : 0.0;
-        const MxStart start = mx_start(lmax, m, nslots, slot, x[t], fac, cfac, jstart, state);
-        ls[t] = start.ls;
-        stv[t] = start.st;
+        slot_of[t] = tile0(t) + lane;
+        x[t] = sx[min(slot_of[t], nslots - 1)];
+    }
+    mx_starts<kAnaMxTiles>(lmax, m, nslots, slot_of, x, fac, cfac, jstart, state, start);
+#pragma unroll
+    for (int t = 0; t < kAnaMxTiles; ++t) {
+        ls[t] = start[t].ls;
+        stv[t] = start[t].st;
         q1[t] = q2[t] = 0.0;
+    }
+#pragma unroll
+    for (int t = 0; t < kAnaMxTiles; ++t) {
         tlo[t] = wave_min(ls[t]);
         thi[t] = wave_max(ls[t] <= lmax ? ls[t] : m);
         mylo = min(mylo, tlo[t]);
