@@ -255,7 +255,7 @@ def power_law_batch(si, lmax, nmaps, config):
 
 
 MX_KERNELS = {"leg_syn": "k_prescale_mx + k_leg_syn_mx", "leg_ana": "k_leg_ana_mx"}
-F64_KERNELS = {"leg_syn": "k_prescale + k_leg_syn", "leg_ana": "k_leg_ana (+ k_ana_combine above 2048 slots)"}
+F64_KERNELS = {"leg_syn": "k_prescale + k_leg_syn", "leg_ana": "k_leg_ana (+ k_ana_finish above 2048 slots)"}
 
 
 def rel_per_map(x, y):
@@ -712,7 +712,7 @@ def main():
         "map2alm_maps_per_s": 1000.0 / (stage_ms["fft_ana"] + stage_ms["leg_ana"]),
         "roofline": {
             "kernel": {"leg_syn": "k_prescale + k_leg_syn",
-                       "leg_ana": "k_leg_ana (+ k_ana_combine above 2048 slots)"}[dom],
+                       "leg_ana": "k_leg_ana (+ k_ana_finish above 2048 slots)"}[dom],
             "bound": "alu",
             "achieved": achieved,
             "peak": PEAK_FP64_VALU_TFLOPS,
