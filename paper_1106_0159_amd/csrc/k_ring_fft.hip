@@ -696,12 +696,17 @@ __device__ __forceinline__ double2 bin_term(double2 dv, int m, const Phase &ph) 
 }
 
 // first + sum over m = m0, m0 + step, .. <= mmax of w_m Delta_m e^{i m phi0},
-// in increasing m (m0 > 0), four loads in flight
+// in increasing m (m0 > 0), four loads in flight.  ONE: a last single term by
+// itself, the whole sum of a ring with n > mmax / 2 (the class 1024 alone: 0.7 of
+// 9.85 us at HEALPix 32 / lmax 64, 16 maps; in the 8192 class it spills, 522 ->
+// 538 us at HEALPix 2048)
+template <bool ONE>
 __device__ __forceinline__ double2 fold_sum(double2 first, const double2 *__restrict__ D, int64_t sm, int m0, int step,
                                             int mmax, const Phase &ph) {
     double cr = first.x, ci = first.y;
+    int m = m0;
 #pragma unroll 1
-    for (int m = m0; m <= mmax; m += 4 * step) {
+    for (; m + (ONE ? step : 0) <= mmax; m += 4 * step) {
         double2 v[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i)
@@ -715,13 +720,19 @@ __device__ __forceinline__ double2 fold_sum(double2 first, const double2 *__rest
             }
         }
     }
+    if (ONE && m <= mmax) {
+        const double2 t = bin_term(D[m * sm], m, ph);
+        cr += t.x;
+        ci += t.y;
+    }
     return make_double2(cr, ci);
 }
 // c_k of one ring: sum over m = k mod n (m <= mmax), given the term of m = k
 // (first, zero if k > mmax)
+template <bool ONE>
 __device__ __forceinline__ double2 fold_bin(double2 first, const double2 *__restrict__ D, int64_t sm, int k, int n,
                                             int mmax, const Phase &ph) {
-    return fold_sum(first, D, sm, k + n, n, mmax, ph);
+    return fold_sum<ONE>(first, D, sm, k + n, n, mmax, ph);
 }
 
 // Column sums of a short ring (n <= NT): with S = n * floor(NT / n), thread
@@ -734,7 +745,7 @@ template <int NT>
 __device__ __forceinline__ void fold_columns(double2 *__restrict__ t, const double2 *__restrict__ D, int64_t sm, int n,
                                              int mmax, const Phase &ph) {
     const int S = n * (NT / n), u = threadIdx.x;
-    if (u < S && u <= mmax) t[u] = fold_sum(bin_term(D[u * sm], u, ph), D, sm, u + S, S, mmax, ph);
+    if (u < S && u <= mmax) t[u] = fold_sum<true>(bin_term(D[u * sm], u, ph), D, sm, u + S, S, mmax, ph);
 }
 // c_k from the column sums: sum_{m = k mod n, m <= lim} t_m, in increasing m
 __device__ __forceinline__ double2 fold_terms(const double2 *__restrict__ t, int k, int n, int lim) {
@@ -860,7 +871,7 @@ __device__ __forceinline__ void half_fold(const double2 *__restrict__ D, int64_t
         for (int i = 0; i < 4; ++i) t[i] = m[i] <= mmax ? D[m[i] * sm] : make_double2(0.0, 0.0);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            if (m[i] <= mmax) t[i] = fold_bin(bin_term(t[i], m[i], ph), D, sm, m[i], N, mmax, ph);
+            if (m[i] <= mmax) t[i] = fold_bin<false>(bin_term(t[i], m[i], ph), D, sm, m[i], N, mmax, ph);
         const double2 a = herm(t[0], t[1]), b = herm(t[2], t[3]);  // h_k, h_{n-k}
         const double2 E = make_double2(a.x + b.x, a.y - b.y);
         const double2 O = cmul(make_double2(a.x - b.x, a.y + b.y), ch.turn(k));
@@ -1031,10 +1042,10 @@ __global__ __launch_bounds__(NT, 4) void k_fft_syn(RingPlan one, const RingPlan 
                 b1 = two ? fold_terms(tb, kn, N, lim) : z;
             } else {
                 // a0..b1 hold the first Delta of each bin (m = k, m = n-k) on entry
-                a0 = fold_bin(k <= mmax ? bin_term(a0, k, pha) : z, Da, dl.s_m, k, N, mmax, pha);
-                a1 = fold_bin(kn <= mmax ? bin_term(a1, kn, pha) : z, Da, dl.s_m, kn, N, mmax, pha);
-                b0 = two ? fold_bin(k <= mmax ? bin_term(b0, k, phb) : z, Db, dl.s_m, k, N, mmax, phb) : z;
-                b1 = two ? fold_bin(kn <= mmax ? bin_term(b1, kn, phb) : z, Db, dl.s_m, kn, N, mmax, phb) : z;
+                a0 = fold_bin<kColumns<MAXL>>(k <= mmax ? bin_term(a0, k, pha) : z, Da, dl.s_m, k, N, mmax, pha);
+                a1 = fold_bin<kColumns<MAXL>>(kn <= mmax ? bin_term(a1, kn, pha) : z, Da, dl.s_m, kn, N, mmax, pha);
+                b0 = two ? fold_bin<kColumns<MAXL>>(k <= mmax ? bin_term(b0, k, phb) : z, Db, dl.s_m, k, N, mmax, phb) : z;
+                b1 = two ? fold_bin<kColumns<MAXL>>(kn <= mmax ? bin_term(b1, kn, phb) : z, Db, dl.s_m, kn, N, mmax, phb) : z;
             }
         };
         // bins k = threadIdx.x + u NT, u = 0 .. U (k = U NT only for thread 0 when
