@@ -31,6 +31,8 @@
  * mirror images (cos theta_r' = -cos theta_r, evaluated from the northern
  * ring) and share one Legendre recurrence; any other ring is evaluated at its
  * own colatitude.
+ * FP64 results (flags 0) of a map do not depend on nmaps, on the map's place
+ * in the call or on the other maps: they are the bits of its own call.
  *
  * Execution: every compute call validates its arguments on the host, then
  * enqueues kernels on `stream` (a hipStream_t; NULL = the null stream) and

@@ -45,10 +45,10 @@
 //              map (or two maps); a wave owns 64 T slots, T per lane, no reduction.
 //   analysis   grid.x = (m, slot group), grid.y = map; a workgroup owns up
 //              to 256 T slots of its m; each wave sums its lanes in registers
-//              and its own LDS rows, the four waves are added in wave order
+//              and its own LDS rows, the waves are added in wave order
 //              every 32 steps, and groups are summed in order by a second
-//              small kernel: no atomics, deterministic.  From three maps on the
-//              sums run on the matrix cores, four maps per workgroup.
+//              small kernel: no atomics, deterministic.  A map's sums do not
+//              depend on the number of maps: its a_lm are the same bits in any call.
 #include <type_traits>
 
 #include "k_device.h"
@@ -480,15 +480,16 @@ __device__ __forceinline__ double quad_sum(double v) {
 }
 
 constexpr int kAnaWaves = kAnaThreads / 64;
-// LDS of an analysis workgroup: wave-private reduction rows, the per-wave
-// chunk sums awaiting a cross-wave flush, and the waves' first starts.
+// LDS of an analysis workgroup of W waves: wave-private reduction rows, the
+// per-wave chunk sums awaiting a cross-wave flush, and the waves' first starts.
+template <int W = kAnaWaves>
 struct AnaLds {
-    alignas(16) SumRows tbuf[kAnaWaves][2];
-    double ring[2][kFlush][kAnaWaves][kVals];
+    alignas(16) SumRows tbuf[W][2];
+    double ring[2][kFlush][W][kVals];
     double carry[2][2];  // S_{j-1} before a flush's first step
-    int wstart[kAnaWaves];
+    int wstart[W];
+    static_assert(kFlush * kVals <= 64 * W, "one thread per flushed value");
 };
-static_assert(kFlush * kVals <= kAnaThreads, "one thread per flushed value");
 
 // The slot operands of one lane, slots slot0 + stride t + lane (t < T, sets of
 // 64 slots): recurrence argument, start, recurrence state and the pair sums
@@ -628,19 +629,19 @@ __device__ __forceinline__ void warm_factors(const ParityFac &f, int64_t jb, int
     }
 }
 
-// Analysis of one m of one map by a workgroup of 4 waves: wave w of group g
-// owns slots ((g T + t) 4 + w) * 64 + lane, t < T (every wave gets sets from
+// Analysis of one m of one map by a workgroup of W waves: wave w of group g
+// owns slots ((g T + t) W + w) * 64 + lane, t < T (every wave gets sets from
 // the whole range of latitudes, so that the waves' work stays even).  Per
 // chunk of kChunk steps each lane sums its T slots; the wave sums its 64 lanes
-// through its own LDS rows (no barrier); every kFlush chunks the 4 wave sums
+// through its own LDS rows (no barrier); every kFlush chunks the W wave sums
 // are added in wave order after one barrier.  The workgroup starts at the
 // earliest start of its slots (a_lm before it get no term).  With one group
 // the finished a_lm are written; otherwise the group's sums go to part[(map *
 // groups + group) * nalm + idx] for k_ana_finish.  Every thread of the
 // workgroup must call it.
-template <int T>
-__device__ __forceinline__ void ana_group(const AnaArgs &A, int m, int grp, int map, int groups, AnaLds &L) {
-    constexpr int kThreads = kAnaThreads;
+template <int T, int W = kAnaWaves>
+__device__ __forceinline__ void ana_group(const AnaArgs &A, int m, int grp, int map, int groups, AnaLds<W> &L) {
+    constexpr int kThreads = 64 * W;
     const int lmax = A.lmax, nj = jcol_len(lmax, m);
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2, jb = jcol_base(lmax, m);
@@ -662,13 +663,13 @@ __device__ __forceinline__ void ana_group(const AnaArgs &A, int m, int grp, int 
     __syncthreads();
     int j0s = nj;
 #pragma unroll
-    for (int w = 0; w < kAnaWaves; ++w) j0s = min(j0s, L.wstart[w]);
+    for (int w = 0; w < W; ++w) j0s = min(j0s, L.wstart[w]);
     j0s = __builtin_amdgcn_readfirstlane(j0s);  // the same in every lane
 
     for (int l = m + tid; l < m + 2 * j0s && l <= lmax; l += kThreads) dst[l] = make_double2(0.0, 0.0);
 
     // Every kFlush chunks (or at the last): thread f < nchunks*kVals takes the
-    // value (chunk f/kVals, v = f%kVals) of the 4 waves' sums and writes it.
+    // value (chunk f/kVals, v = f%kVals) of the W waves' sums and writes it.
     auto flush = [&](int jbase, int par, int nchunks) {
         const int fk = tid / kVals, fv = tid % kVals, fc = tid & 3;
         const int j = jbase + (tid >> 2), l = m + 2 * j + (fc >> 1);
@@ -683,7 +684,7 @@ __device__ __forceinline__ void ana_group(const AnaArgs &A, int m, int grp, int 
             auto total = [&](int chunk, int v) {
                 double t = 0.0;
 #pragma unroll
-                for (int u = 0; u < kAnaWaves; ++u) t += L.ring[par][chunk][u][v];
+                for (int u = 0; u < W; ++u) t += L.ring[par][chunk][u][v];
                 return t;
             };
             double v = total(fk, fv);
@@ -803,12 +804,12 @@ __device__ __forceinline__ void ana_wave(const AnaArgs &A, int m, int map, SumRo
 // map.  Three waves per SIMD at 8 slots per lane (168 VGPRs, 7 of them spilled
 // outside the chunk loop) run faster than two without the spills: 589 against
 // 637 us at HEALPix 1024 / lmax 2048.
-template <int T>
-__global__ __launch_bounds__(kAnaThreads, T <= 4 ? 4 : 3) void k_leg_ana(AnaArgs A, int groups) {
-    __shared__ AnaLds L;
+template <int T, int W>
+__global__ __launch_bounds__(64 * W, T <= 4 ? 4 : 3) void k_leg_ana(AnaArgs A, int groups) {
+    __shared__ AnaLds<W> L;
     const MPart mp = xcd_m_part(groups);
     if (mp.m > A.mmax) return;  // padding of the m range (whole workgroup, before any barrier)
-    ana_group<T>(A, mp.m, mp.part, (int)blockIdx.y, groups, L);
+    ana_group<T, W>(A, mp.m, mp.part, (int)blockIdx.y, groups, L);
 }
 // At most 64 slots, one wave per m: grid.x = m in the XCD-aware order, grid.y = map.
 __global__ __launch_bounds__(64) void k_leg_ana_wave(AnaArgs A) {
@@ -816,214 +817,6 @@ __global__ __launch_bounds__(64) void k_leg_ana_wave(AnaArgs A) {
     const MPart mp = xcd_m_part(1);
     if (mp.m > A.mmax) return;
     ana_wave<1>(A, mp.m, (int)blockIdx.y, tb);
-}
-
-// ---------------------------------------------------------------- batches: FP64 matrix cores
-// Analysis of four maps at once with the sums over the rings on the FP64
-// matrix cores: for each step j the sums S and T of the four maps are 16
-// columns, so 16 steps by 16 columns are one 16x16 matrix product over the
-// rings (v_mfma_f64_16x16x4_f64: rows are steps, columns 4 map + {S re, S im,
-// T re, T im}, k the ring slots), accumulated in the FP64 of the vector units
-// (the instruction adds its four products as a chain of fused multiply-adds).
-// A wave owns T sets of 64 slots; their D+ and x D- operands stay in registers
-// for the whole kernel (32 VGPRs per set).  Per chunk of 16 steps a set's lanes
-// run the recurrence, one slot each, and hand their q through the wave's LDS
-// tile, which turns lanes (slots) into the k of the product; the sum over the
-// lanes that costs the vector kernel a third of its instructions is part of
-// the product, and the recurrence is shared by the four maps.
-// Bound: the matrix unit, 16 instructions of 64 cycles per set and chunk
-// against about 200 cycles of vector work (an FP64 matrix stream reaches 68
-// TFLOP/s on this part, an FP64 FMA stream 72 to 77, and they share the unit);
-// it is busy 45 % of the time at 1025 x 2049 rings, lmax 1024.  Stage for 64
-// maps there: 1.96 ms, with one map at a time on the vector units 4.60; 4 maps
-// at HEALPix 512 / lmax 1024 0.227 and 0.416; 8 at 1024 / 2048 2.88 and 4.09.
-// Three waves per SIMD up to 3 sets per wave: two cost 2.41 ms instead of 1.96.
-// Delta comes in one slot per lane and 16 bytes per load, through the q tile,
-// because the operand layout read directly takes 32 scattered 8-byte loads per
-// set (4.25 ms).  The coefficients of a chunk are loaded once, a chunk ahead.
-static_assert(kStartJ == 4, "an operand's row block is one run between starts");
-constexpr int kMmStep = 16;           // recurrence steps per chunk
-constexpr int kMmMaps = 4;            // maps per workgroup
-constexpr int kMmRow = 64 + 2;        // doubles per step of a q tile (the padding keeps the operand reads conflict-free)
-constexpr int kMmDRow = 16 + 2;        // doubles per slot while Delta passes through the tile
-constexpr int kMmTile = 64 * kMmDRow;  // doubles of a wave's tile
-static_assert(kMmStep * kMmRow <= kMmTile, "q tile");
-constexpr int kMmSets = 4;            // sets of 64 slots per wave, at most
-typedef double dvec4 __attribute__((ext_vector_type(4)));
-
-template <int T, int W>
-__global__ __launch_bounds__(64 * W, W == 4 ? (T <= 3 ? 3 : 2) : 2) void k_leg_ana_mm(AnaArgs A, int groups, int nmaps) {
-    constexpr int kThreads = 64 * W;
-    __shared__ alignas(16) double qt[W][kMmTile];
-    __shared__ double red[2][W][kMmStep][16];
-    __shared__ double carry[2][16];  // S_{j-1} before a chunk's first step, per column
-    __shared__ int wstart[W];
-
-    const MPart mp = xcd_m_part(groups);
-    const int m = mp.m, grp = mp.part;
-    if (m > A.mmax) return;  // padding of the m range (whole workgroup, before any barrier)
-    const int lmax = A.lmax, nslots = A.nslots, nj = jcol_len(lmax, m);
-    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int col = lane & 15, kq = lane >> 4;  // operand column (or row) and k group of this lane
-    const int map0 = blockIdx.y * kMmMaps;
-    const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2, jb = jcol_base(lmax, m);
-    const double warm_a = warm_l2(A.ra + jb, 1, 0, nj - 1), warm_b = warm_l2(A.rb + jb, 1, 0, nj - 1);
-    if (groups == 1) warm_factors<kThreads>(A.fac, jb, nj);
-
-    // set t of wave w holds slots ((grp T + t) W + w) * 64 .. + 63 (every wave
-    // gets sets from the whole range of latitudes); polar sets lie below npolar
-    auto set0 = [&](int t) { return ((grp * T + t) * W + wv) * 64; };
-    double w[T], q1[T], q2[T], dv[T][16];
-    int js[T], slo[T];
-    int lo = kNeverJ;
-    // Delta of the maps, one slot per lane; D+ and x D- pass through the wave's
-    // tile into the operand layout (operand u: slot 16 kq + u, this lane's column)
-    double *tile = qt[wv];
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-        const int slot = set0(t) + lane, sl = min(slot, nslots - 1);
-        const bool act = slot < nslots;
-        const int r1 = A.rn[sl], r2 = A.rsouth[sl], js0 = A.jstart[(int64_t)m * nslots + sl];
-        const double2 st = A.state[(int64_t)m * nslots + sl];
-        const double x = A.sx[sl];
-        w[t] = A.sw[sl];
-        js[t] = act && js0 < nj ? js0 : kNeverJ;
-        q2[t] = st.x;
-        q1[t] = st.y;
-        double2 dn[kMmMaps], ds[kMmMaps];
-#pragma unroll
-        for (int i = 0; i < kMmMaps; ++i) {
-            dn[i] = ds[i] = make_double2(0.0, 0.0);
-            if (js[t] < nj && map0 + i < nmaps) {
-                const double2 *d = A.delta + (int64_t)(map0 + i) * A.nrings * (A.mmax + 1) + m;
-                dn[i] = d[(int64_t)r1 * (A.mmax + 1)];
-                if (r2 >= 0) ds[i] = d[(int64_t)r2 * (A.mmax + 1)];
-            }
-        }
-        slo[t] = wave_min(js[t]);
-        lo = min(lo, slo[t]);
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int i = 0; i < kMmMaps; ++i) {
-            double2 *row = reinterpret_cast<double2 *>(tile + lane * kMmDRow + 4 * i);
-            row[0] = make_double2(dn[i].x + ds[i].x, dn[i].y + ds[i].y);
-            row[1] = make_double2(x * (dn[i].x - ds[i].x), x * (dn[i].y - ds[i].y));
-        }
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int u = 0; u < 16; ++u) dv[t][u] = tile[(16 * kq + u) * kMmDRow + col];
-        __builtin_amdgcn_wave_barrier();
-        asm volatile("" ::: "memory");
-    }
-    asm volatile("" ::"v"(warm_a), "v"(warm_b));
-    if (lane == 0) wstart[wv] = lo;
-    if (tid < 32) carry[tid >> 4][tid & 15] = 0.0;
-    __syncthreads();
-    int j0s = nj;
-#pragma unroll
-    for (int i = 0; i < W; ++i) j0s = min(j0s, wstart[i]);
-    j0s = __builtin_amdgcn_readfirstlane(j0s);
-
-    auto out = [&](int mapi, int l) {
-        return groups == 1 ? A.alm + (int64_t)mapi * A.nalm + base + l
-                           : A.part + ((int64_t)mapi * groups + grp) * A.nalm + base + l;
-    };
-    for (int i = tid; i < kMmMaps * 2 * j0s; i += kThreads) {  // no slot of the group has started: no term
-        const int l = m + i / kMmMaps, mapi = map0 + i % kMmMaps;
-        if (l <= lmax && mapi < nmaps) *out(mapi, l) = make_double2(0.0, 0.0);
-    }
-
-    // The coefficients of a chunk stay in scalar registers; the next chunk's are
-    // loaded once the last set's recurrence is done, under its matrix work and
-    // the exchange between the waves.
-    const const_ptr<double> ra = ro(A.ra + jb), rb = ro(A.rb + jb), rbp = ro(A.rbp + jb);
-    static_assert(2 * kMmStep <= kCoefPad, "coefficient padding too short");
-    const bool polar0 = set0(0) < A.npolar;  // the polar slots are a wave's first set
-    double ca[kMmStep], cb[kMmStep];
-    auto load = [&](int j) {
-#pragma unroll
-        for (int i = 0; i < kMmStep; ++i) {
-            ca[i] = ra[j + i];
-            cb[i] = rb[j + i];
-        }
-        asm volatile("" ::: "memory");
-    };
-    load(j0s);
-    int buf = 0;
-    for (int j0 = j0s; j0 < nj; j0 += kMmStep) {
-        dvec4 acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-            const bool started = slo[t] < j0 + kMmStep;  // else all q are 0
-            if (started) {
-#pragma unroll
-                for (int g = 0; g < kMmStep; g += kStartJ) {
-                    // starts are multiples of kStartJ; a slot that has not started
-                    // gives zeros and keeps its state (steps past the column's end
-                    // read the next column's coefficients or the padding: unused)
-                    double q[kStartJ] = {0.0, 0.0, 0.0, 0.0};
-                    if (j0 + g >= js[t]) {
-#pragma unroll
-                        for (int i = 0; i < kStartJ; ++i) {
-                            double aj = ca[g + i];
-                            asm("" : "+v"(aj));
-                            const double bj = t == 0 && polar0 ? rbp[j0 + g + i] : cb[g + i];
-                            q[i] = fma(fma(aj, w[t], bj), q1[t], -q2[t]);
-                            q2[t] = q1[t];
-                            q1[t] = q[i];
-                        }
-                    }
-#pragma unroll
-                    for (int i = 0; i < kStartJ; ++i) tile[(g + i) * kMmRow + lane] = q[i];
-                }
-            }
-            if (t == T - 1) load(j0 + kMmStep);
-            if (!started) continue;
-            // LDS operations of one wave complete in order: the reads see the
-            // writes above, and the next set's writes follow these reads
-            __builtin_amdgcn_wave_barrier();
-            dvec4 part = {0.0, 0.0, 0.0, 0.0};  // a chain of 64 products per set
-#pragma unroll
-            for (int u = 0; u < 16; u += 2) {
-                const dvec2 a = *reinterpret_cast<const dvec2 *>(&tile[col * kMmRow + 16 * kq + u]);
-                part = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, dv[t][u], part, 0, 0, 0);
-                part = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, dv[t][u + 1], part, 0, 0, 0);
-            }
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int r = 0; r < 4; ++r)  // an infinite or NaN Delta (times q = 0) stays out of the steps before the set's start
-                if (j0 + kStartJ * r >= slo[t]) acc[r] += part[r];
-        }
-        // lane (col, kq) holds steps kq + 4 r of its column
-#pragma unroll
-        for (int r = 0; r < 4; ++r) red[buf][wv][kq + 4 * r][col] = acc[r];
-        // value (step i, column c) of the chunk: thread 16 i + c
-        const int i = (tid >> 4) & 15, c = tid & 15, fc = c & 3;
-        const int j = j0 + i, l = m + 2 * j + (fc >> 1), mapi = map0 + (c >> 2);
-        double f0 = 0.0, f1 = 0.0;  // loaded ahead of the barrier
-        if (groups == 1 && j < nj) {
-            f0 = fc < 2 ? A.fac.pe1[jb + j] : A.fac.po[jb + j];
-            if (fc < 2 && j > 0) f1 = A.fac.pe2[jb + j - 1];
-        }
-        __syncthreads();
-        if (tid < 256) {
-            auto total = [&](int step) {
-                double v = 0.0;
-#pragma unroll
-                for (int u = 0; u < W; ++u) v += red[buf][u][step][c];
-                return v;
-            };
-            double v = total(i);
-            if (groups == 1) {
-                const double before = i > 0 ? total(i - 1) : carry[buf][c];
-                if (i == kMmStep - 1) carry[buf ^ 1][c] = v;
-                v = fc < 2 ? fma(f0, v, f1 * before) : f0 * v;
-                if (m == 0 && (fc & 1)) v = 0.0;
-            }
-            if (l <= lmax && mapi < nmaps) reinterpret_cast<double *>(out(mapi, l))[fc & 1] = v;
-        }
-        buf ^= 1;  // the next chunk writes the other buffer while this one may still be read
-    }
 }
 
 // FP64 analysis with several groups: the sums S_j, T_j of a column are
@@ -1073,7 +866,7 @@ __global__ __launch_bounds__(kBlock) void k_ana_combine(int64_t nalm, int lmax, 
 __global__ __launch_bounds__(kBlock, 3) void k_leg_batch(const BatchReq *__restrict__ reqs,
                                                        const BatchItem *__restrict__ items, int nitems,
                                                        int *__restrict__ head) {
-    __shared__ AnaLds L;
+    __shared__ AnaLds<> L;
     __shared__ int s_idx;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -1193,16 +986,6 @@ int launch_prescale(const CoefTables &c, const void *alm, void *aprime, int nmap
 }
 
 constexpr int kSynSlotsPerLane = 4;
-// Analysis on the matrix cores from 3 maps on (a workgroup's cost is that of
-// four; stage, matrix and vector form: 3 maps at HEALPix 1024 / lmax 2048 1409
-// and 1567 us, at 347 / 694 122 and 162; two maps 120 and 109 at 347 / 694,
-// 230 and 277 at 512 / 1024, 1450 and 1100 at 1024 / 2048) and above 64 slots
-// (64 and below: one wave per m and map without barriers).  One or two maps
-// left over take the vector form from kMmTailSlots on; below, the launch is
-// too short for a second one to pay (257 rings, 5 maps: 24 us, one map 22).
-constexpr int kMmMinMaps = 3, kMmMinSlots = 64, kMmTailSlots = 512;
-static_assert(8 * kMmSets * 64 == kAnaThreads * kAnaSlotsPerThread, "the matrix form's groups are those of ana_groups");
-
 template <int T, int M>
 static int launch_syn_mm(const SynArgs &A, int nslots, int mmax, int nmaps, hipStream_t st) {
     const int tiles = (nslots + kBlock * T - 1) / (kBlock * T);
@@ -1248,25 +1031,10 @@ int launch_leg_syn(const CoefTables &c, const GeomPlan &p, const StartTable &s, 
     return SHT_OK;
 }
 
-template <int T, int W>
-static void launch_ana_mm_t(const AnaArgs &A, int groups, int nmaps, hipStream_t st) {
-    hipLaunchKernelGGL((k_leg_ana_mm<T, W>), dim3((unsigned)(padded_m(A.mmax) * groups), (unsigned)((nmaps + kMmMaps - 1) / kMmMaps)),
-                       dim3(64 * W), 0, st, A, groups, nmaps);
-}
-template <int W>
-static void launch_ana_mm(const AnaArgs &A, int T, int groups, int nmaps, hipStream_t st) {
-    switch (T) {
-        case 1: launch_ana_mm_t<1, W>(A, groups, nmaps, st); break;
-        case 2: launch_ana_mm_t<2, W>(A, groups, nmaps, st); break;
-        case 3: launch_ana_mm_t<3, W>(A, groups, nmaps, st); break;
-        default: launch_ana_mm_t<4, W>(A, groups, nmaps, st); break;
-    }
-}
-
-template <int T>
+template <int T, int W = kAnaWaves>
 static void launch_ana_t(const AnaArgs &A, int groups, int nmaps, hipStream_t st) {
-    hipLaunchKernelGGL(k_leg_ana<T>, dim3((unsigned)(padded_m(A.mmax) * groups), (unsigned)nmaps), dim3(kAnaThreads), 0,
-                       st, A, groups);
+    hipLaunchKernelGGL((k_leg_ana<T, W>), dim3((unsigned)(padded_m(A.mmax) * groups), (unsigned)nmaps), dim3(64 * W), 0, st,
+                       A, groups);
 }
 
 int launch_leg_ana(const CoefTables &c, const GeomPlan &p, const StartTable &s, const void *delta, void *alm,
@@ -1277,38 +1045,31 @@ int launch_leg_ana(const CoefTables &c, const GeomPlan &p, const StartTable &s, 
     if (!grid_ok((int64_t)padded_m(c.mmax) * groups)) return SHT_EUNSUPPORTED;
     if (groups > 1 && !partials) return SHT_EWORKSPACE;
     const AnaArgs A = ana_args(c, p, s, delta, alm, partials);
-    // maps [0, nmm) on the matrix cores, the others one at a time
-    int nmm = nmaps >= kMmMinMaps && p.nslots > kMmMinSlots ? nmaps : 0;
-    if (nmm && p.nslots > kMmTailSlots && nmaps % kMmMaps < kMmMinMaps) nmm -= nmaps % kMmMaps;
-    if (nmm) {
-        const int sets = (p.nslots + 63) / 64;
-        if (sets <= 4 * kMmSets)
-            launch_ana_mm<4>(A, (sets + 3) / 4, groups, nmm, st);
-        else
-            launch_ana_mm<8>(A, groups > 1 ? kMmSets : (sets + 7) / 8, groups, nmm, st);
-        SHT_HIP(hipGetLastError());
-    }
-    if (nmm < nmaps) {
-        AnaArgs V = A;
-        V.delta += (int64_t)nmm * p.nrings * (c.mmax + 1);
-        V.alm += (int64_t)nmm * c.nalm;
-        if (groups > 1) V.part += (int64_t)nmm * groups * c.nalm;
-        const int rest = nmaps - nmm;
-        if (p.nslots <= 64) {
-            // one wave holds every slot: no step across waves (lmax 64 on 64
-            // slots: 10.2 us for the stage against 11.6 with a workgroup)
-            hipLaunchKernelGGL(k_leg_ana_wave, dim3((unsigned)padded_m(c.mmax), (unsigned)rest), dim3(64), 0, st, V);
-        } else {
-            switch (T) {
-                case 1: launch_ana_t<1>(V, groups, rest, st); break;
-                case 2: launch_ana_t<2>(V, groups, rest, st); break;
-                case 3: launch_ana_t<3>(V, groups, rest, st); break;
-                case 4: launch_ana_t<4>(V, groups, rest, st); break;
-                case 5: launch_ana_t<5>(V, groups, rest, st); break;
-                case 6: launch_ana_t<6>(V, groups, rest, st); break;
-                case 7: launch_ana_t<7>(V, groups, rest, st); break;
-                default: launch_ana_t<kAnaSlotsPerThread>(V, groups, rest, st); break;
-            }
+    // The form depends on the slots alone, not on the number of maps: a map's
+    // a_lm are the same bits in any call.
+    if (p.nslots <= 64) {
+        // one wave holds every slot: no step across waves (lmax 64 on 64
+        // slots: 10.2 us for the stage against 11.6 with a workgroup)
+        hipLaunchKernelGGL(k_leg_ana_wave, dim3((unsigned)padded_m(c.mmax), (unsigned)nmaps), dim3(64), 0, st, A);
+    } else if (p.nslots > 512 && p.nslots <= 640) {
+        // Two waves of 5 slots per lane add half the wave sums of four waves of
+        // 3: 64 maps on 513 slots, lmax 1024, 3.51 against 4.69 ms for the
+        // stage, one map 115 against 107 us.  Up to 512 slots one map leaves
+        // the chip with too few waves for that, and from 641 on (6 per lane) it
+        // costs one map more than it gives several (694 slots, lmax 694: one
+        // map 82 and 68 us, eight 289 and 338).
+        static_assert(5 * 2 * 64 == 640, "one group");
+        launch_ana_t<5, 2>(A, groups, nmaps, st);
+    } else {
+        switch (T) {
+            case 1: launch_ana_t<1>(A, groups, nmaps, st); break;
+            case 2: launch_ana_t<2>(A, groups, nmaps, st); break;
+            case 3: launch_ana_t<3>(A, groups, nmaps, st); break;
+            case 4: launch_ana_t<4>(A, groups, nmaps, st); break;
+            case 5: launch_ana_t<5>(A, groups, nmaps, st); break;
+            case 6: launch_ana_t<6>(A, groups, nmaps, st); break;
+            case 7: launch_ana_t<7>(A, groups, nmaps, st); break;
+            default: launch_ana_t<kAnaSlotsPerThread>(A, groups, nmaps, st); break;
         }
     }
     SHT_HIP(hipGetLastError());
