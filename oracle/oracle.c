@@ -12,7 +12,8 @@
  * (eqs. Delta2map, almfftdef), with the azimuthal sums done as plain DFTs
  * (no FFT) and every loop in ascending index order.  Arithmetic is plain
  * double precision (built with -ffp-contract=off, so no fused operations);
- * long double is used only to build phase factors and the mu_m seeds.
+ * long double is used to build phase factors and the mu_m seeds, and for the
+ * Legendre functions of rings next to a pole (R7).
  *
  * Readings of the paper's formulas used here:
  *  R1 (eq. assLegRec) the recurrence is
@@ -36,6 +37,12 @@
  *     point, where lambda_lm only grows with l.  Power-of-two scaling is
  *     exact, so each term equals the infinite-exponent-range recurrence; it is
  *     converted to a double with ldexp (gradual underflow).
+ *  R7 (rings next to a pole) cos(theta) rounded to a double moves a ring with
+ *     small sin(theta) by up to 2^-54 / sin(theta), which at lmax 2048 changes
+ *     the values of the first rings of HEALPix N_side 1024 by 1e-11 and more, and beta_lm
+ *     rounded to a double by about 1e-12.  Where sin(theta) < POLAR_SIN the
+ *     whole recurrence (cos, sin, beta, seeds, steps) is therefore carried in
+ *     long double and each lambda_lm rounded once.
  */
 #include "oracle.h"
 
@@ -47,6 +54,7 @@
 #define SCALE_BITS 256
 static const double BIG = 0x1p256;
 static const double SMALL = 0x1p-256;
+#define POLAR_SIN 0.125
 static const long double PI_L = 3.141592653589793238462643383279502884L;
 
 typedef struct {
@@ -157,6 +165,63 @@ static void plm_run(int lmax, int m, double x, xdbl seed, const double *beta,
     }
 }
 
+/* The same recurrence in long double (R7), rounded to doubles at the end. */
+typedef struct {
+    long double f; /* value = f * 2^(SCALE_BITS*k) */
+    int k;
+} xldbl;
+
+static int is_polar(double theta) { return sin(theta) < POLAR_SIN; }
+
+static void beta_tables_l(int lmax, int mmax, long double *beta, long double *ratio) {
+#pragma omp parallel for num_threads(oracle_get_threads()) schedule(dynamic, 8)
+    for (int m = 0; m <= mmax; ++m) {
+        long double *b = beta + alm_idx(m, m, lmax), *q = ratio + alm_idx(m, m, lmax);
+        b[0] = q[0] = 0.0L;
+        for (int l = m + 1; l <= lmax; ++l) {
+            long double ll = l, mm = m;
+            b[l - m] = sqrtl((4.0L * ll * ll - 1.0L) / (ll * ll - mm * mm));
+            q[l - m] = (l >= m + 2) ? b[l - m] / b[l - m - 1] : 0.0L;
+        }
+    }
+}
+
+static void seed_row_l(int mmax, long double s, xldbl *seed) {
+    long double pf = 1.0L, mu = 1.0L / sqrtl(4.0L * PI_L); /* sin^m = pf * 2^pe */
+    long pe = 0;
+    for (int m = 0; m <= mmax; ++m) {
+        if (m > 0) {
+            int e;
+            pf = frexpl(pf * s, &e);
+            pe += e;
+            mu *= sqrtl((long double)(2 * m + 1) / (long double)(2 * m));
+        }
+        long double f = ((m & 1) ? -mu : mu) * pf;
+        long k = (pe >= 0) ? 0 : -((-pe) / SCALE_BITS);
+        seed[m].f = (f == 0.0L) ? 0.0L : ldexpl(f, (int)(pe - (long)SCALE_BITS * k));
+        seed[m].k = (f == 0.0L) ? 0 : (int)k;
+    }
+}
+
+/* v[l - m] = lambda_lm(x), l = m..lmax */
+static void plm_run_l(int lmax, int m, long double x, xldbl seed, const long double *beta,
+                      const long double *ratio, double *v) {
+    long double p2 = seed.f, p1 = 0.0L;
+    int k = seed.k;
+    v[0] = (double)ldexpl(p2, SCALE_BITS * k);
+    for (int l = m + 1; l <= lmax; ++l) {
+        long double p = (l == m + 1) ? beta[1] * x * p2 : beta[l - m] * x * p1 - ratio[l - m] * p2;
+        if (l > m + 1) p2 = p1;
+        p1 = p;
+        if (fabsl(p1) >= 0x1p256L) {
+            p1 *= 0x1p-256L;
+            p2 *= 0x1p-256L;
+            k += 1;
+        }
+        v[l - m] = (double)(k == 0 ? p1 : ldexpl(p1, SCALE_BITS * k));
+    }
+}
+
 int oracle_plm_ext(int lmax, int m, double theta, double *mant, int32_t *exp2) {
     if (lmax < 0 || m < 0 || m > lmax || !mant || !exp2) return -1;
     if (!(theta >= 0.0 && theta <= M_PI)) return -1;
@@ -212,23 +277,39 @@ int oracle_delta_syn(int lmax, int mmax, int nrings, const double *theta,
     double *mu = malloc(sizeof(double) * (mmax + 1));
     beta_tables(lmax, mmax, beta, ratio);
     mu_table(mmax, mu);
+    int polar = 0;
+    for (int i = 0; i < nsel; ++i) polar |= is_polar(theta[ring_sel ? ring_sel[i] : i]);
+    long double *beta_l = NULL, *ratio_l = NULL;
+    if (polar) {
+        beta_l = malloc(sizeof(long double) * na);
+        ratio_l = malloc(sizeof(long double) * na);
+        beta_tables_l(lmax, mmax, beta_l, ratio_l);
+    }
 #pragma omp parallel num_threads(oracle_get_threads())
     {
         xdbl *seed = malloc(sizeof(xdbl) * (mmax + 1));
+        xldbl *seed_l = malloc(sizeof(xldbl) * (mmax + 1));
         double *f = malloc(sizeof(double) * (lmax + 1));
         int *k = malloc(sizeof(int) * (lmax + 1));
 #pragma omp for schedule(dynamic, 1)
         for (int i = 0; i < nsel; ++i) {
             int r = ring_sel ? ring_sel[i] : i;
             double x = cos(theta[r]);
-            seed_row(mmax, sin(theta[r]), mu, seed);
+            int ext = is_polar(theta[r]);
+            if (ext)
+                seed_row_l(mmax, sinl((long double)theta[r]), seed_l);
+            else
+                seed_row(mmax, sin(theta[r]), mu, seed);
             for (int m = 0; m <= mmax; ++m) {
                 int64_t b = alm_idx(m, m, lmax);
-                plm_run(lmax, m, x, seed[m], beta + b, ratio + b, f, k);
+                if (ext)
+                    plm_run_l(lmax, m, cosl((long double)theta[r]), seed_l[m], beta_l + b, ratio_l + b, f);
+                else
+                    plm_run(lmax, m, x, seed[m], beta + b, ratio + b, f, k);
                 const double *a = alm + 2 * alm_idx(0, m, lmax);
                 double dre = 0.0, dim = 0.0;
                 for (int l = m; l <= lmax; ++l) {
-                    double v = xval(f[l - m], k[l - m]);
+                    double v = ext ? f[l - m] : xval(f[l - m], k[l - m]);
                     dre += a[2 * l] * v;
                     if (m > 0) dim += a[2 * l + 1] * v; /* R5: Im a_l0 ignored */
                 }
@@ -236,9 +317,9 @@ int oracle_delta_syn(int lmax, int mmax, int nrings, const double *theta,
                 out[2 * ((int64_t)i * (mmax + 1) + m) + 1] = dim;
             }
         }
-        free(seed); free(f); free(k);
+        free(seed); free(seed_l); free(f); free(k);
     }
-    free(beta); free(ratio); free(mu);
+    free(beta); free(ratio); free(mu); free(beta_l); free(ratio_l);
     return 0;
 }
 
@@ -393,10 +474,24 @@ int oracle_delta2alm(int lmax, int mmax, int nrings, const double *theta,
     /* seeds for every ring and m <= mtop */
     xdbl *seeds = malloc(sizeof(xdbl) * (size_t)nrings * (mtop + 1));
     double *xs = malloc(sizeof(double) * nrings);
+    int *ext = malloc(sizeof(int) * nrings); /* index among the rings of R7, or -1 */
+    int npolar = 0;
+    for (int r = 0; r < nrings; ++r) ext[r] = is_polar(theta[r]) ? npolar++ : -1;
+    long double *beta_l = NULL, *ratio_l = NULL;
+    xldbl *seeds_l = NULL;
+    if (npolar) {
+        beta_l = malloc(sizeof(long double) * na);
+        ratio_l = malloc(sizeof(long double) * na);
+        seeds_l = malloc(sizeof(xldbl) * (size_t)npolar * (mtop + 1));
+        beta_tables_l(lmax, mmax, beta_l, ratio_l);
+    }
 #pragma omp parallel for num_threads(oracle_get_threads()) schedule(static)
     for (int r = 0; r < nrings; ++r) {
         xs[r] = cos(theta[r]);
-        seed_row(mtop, sin(theta[r]), mu, seeds + (size_t)r * (mtop + 1));
+        if (ext[r] >= 0)
+            seed_row_l(mtop, sinl((long double)theta[r]), seeds_l + (size_t)ext[r] * (mtop + 1));
+        else
+            seed_row(mtop, sin(theta[r]), mu, seeds + (size_t)r * (mtop + 1));
     }
 #pragma omp parallel num_threads(oracle_get_threads())
     {
@@ -409,12 +504,16 @@ int oracle_delta2alm(int lmax, int mmax, int nrings, const double *theta,
             int nl = lmax - m + 1;
             memset(acc, 0, sizeof(double) * 2 * nl);
             for (int r = 0; r < nrings; ++r) { /* ascending r */
-                plm_run(lmax, m, xs[r], seeds[(size_t)r * (mtop + 1) + m], beta + alm_idx(m, m, lmax),
-                        ratio + alm_idx(m, m, lmax), f, k);
+                int64_t b = alm_idx(m, m, lmax);
+                if (ext[r] >= 0)
+                    plm_run_l(lmax, m, cosl((long double)theta[r]), seeds_l[(size_t)ext[r] * (mtop + 1) + m],
+                              beta_l + b, ratio_l + b, f);
+                else
+                    plm_run(lmax, m, xs[r], seeds[(size_t)r * (mtop + 1) + m], beta + b, ratio + b, f, k);
                 double dre = delta[2 * ((int64_t)r * nm + i)];
                 double dim = delta[2 * ((int64_t)r * nm + i) + 1];
                 for (int l = m; l <= lmax; ++l) {
-                    double v = xval(f[l - m], k[l - m]);
+                    double v = ext[r] >= 0 ? f[l - m] : xval(f[l - m], k[l - m]);
                     acc[2 * (l - m)] += dre * v;
                     acc[2 * (l - m) + 1] += dim * v;
                 }
@@ -428,6 +527,7 @@ int oracle_delta2alm(int lmax, int mmax, int nrings, const double *theta,
         free(f); free(k); free(acc);
     }
     free(seeds); free(xs); free(beta); free(ratio); free(mu);
+    free(ext); free(beta_l); free(ratio_l); free(seeds_l);
     return 0;
 }
 

@@ -255,11 +255,8 @@ static void coef_column(int lmax, int m, double *alpha, double *cfac) {
 // the coefficient of q_{j-1} is -1; C_j is carried in long double, so that its
 // rounding stays out of the recurrence.
 //
-// ra, rb (slots away from the poles) take beta and rho in long double.  rbp (the
-// GeomPlan::npolar slots next to the poles) takes them rounded to double, as a
-// direct evaluation of eq. betaDef has them: with colatitudes that close to the
-// pole rounded to double as well (build_slots), both roundings move a ring of a few
-// pixels by about 1e-12, and the FP64 path moves it as eq. assLegRec in double does.
+// rbp = A_j + B_j goes with the argument x^2 - 1 of the slots next to the poles
+// (GeomPlan::npolar).  All are formed in long double and rounded once.
 static void x2_column(int lmax, int m, double *ra, double *rb, double *rbp, double *pe1, double *pe2, double *po) {
     const int n = jcol_len(lmax, m);
     ra[0] = rb[0] = rbp[0] = 0.0;
@@ -283,30 +280,13 @@ static void x2_column(int lmax, int m, double *ra, double *rb, double *rbp, doub
                 const long double a = c1 / c2 * hinv;
                 ra[j + 1] = (double)a;
                 rb[j + 1] = (double)(-a * (i0 * i0 + i1 * i1));
+                rbp[j + 1] = (double)(a * (1.0L - i0 * i0 - i1 * i1));
             }
             c0 = c1;
             c1 = c2;
             h0 = h;
             b0 = b2;
         }
-    }
-    auto beta = [m](int l) {
-        const double L = l, M = m;
-        return std::sqrt((4.0 * L * L - 1.0) / (L * L - M * M));
-    };
-    long double c0 = 1.0L, c1 = 1.0L;
-    double b0 = beta(m + 1), rho0 = 0.0;  // beta_k, rho_k (rho_{m+1} is never used)
-    for (int j = 0; j + 1 < n; ++j) {
-        const int k = m + 2 * j + 1;
-        const double b1 = beta(k + 1), b2 = beta(k + 2), rho1 = b1 / b0, rho2 = b2 / b1;
-        const long double v = (long double)b2 * rho1 / b0;
-        const long double c2 = j == 0 ? 1.0L : v * rho0 * c0;  // differs from the C_{j+1} above by a few 1e-15 at most
-        const long double f = c1 / c2, a = (long double)b2 * b1 * f;
-        rbp[j + 1] = (double)(a - (v + rho2) * f);
-        c0 = c1;
-        c1 = c2;
-        b0 = b2;
-        rho0 = rho2;
     }
 }
 
@@ -685,10 +665,8 @@ static SlotTables build_slots(const HostGeom &h) {
     for (const S &s : slots) {
         const long double th = h.theta[s.n], sn = sinl(th);
         const double c = std::cos(h.theta[s.n]);
-        // the polar half of the polar slots is evaluated at cos(theta) rounded
-        // to a double, the others at cos(theta)^2 itself, rounded once
-        const long double cl = (int)t.w.size() < t.npolar / 2 ? (long double)c : cosl(th), c2 = cl * cl;
-        t.w.push_back((int)t.w.size() < t.npolar ? (double)(c2 - 1.0L) : (double)c2);
+        const long double cl = cosl(th);
+        t.w.push_back((int)t.w.size() < t.npolar ? (double)(-sn * sn) : (double)(cl * cl));
         t.x.push_back(c);
         t.s.push_back(make_double2((double)sn, (double)(sn - (long double)(double)sn)));
         t.north.push_back(s.n);
