@@ -7,22 +7,21 @@
 // (eq. pmm, with the exponent m/2 and the Condon-Shortley phase) and
 // lambda_{m+1,m} = sqrt(2m+3) x lambda_mm (eq. pm1m).
 //
-// The recurrence steps by two in l and runs in x^2 (the idea of Ishioka, J.
-// Meteorol. Soc. Japan 96, 2018): with eps_l = 1/beta_l, r_j =
-// lambda_{m+2j+1,m} / x is a polynomial in x^2 times sin^m(theta), and after
-// rescaling r_j = C_j q_j its three-term recurrence reads
-//   q_j = (A_j x^2 + B_j) q_{j-1} - q_{j-2},
-// two fused multiply-adds for two degrees l.  Both parities come from q_j:
-//   lambda_{m+2j+1} = C_j x q_j,
-//   lambda_{m+2j}   = C_j eps_{m+2j+1} q_j + C_{j-1} eps_{m+2j} q_{j-1}.
-// Synthesis folds these factors into a_lm once per call (k_prescale): with
-// e_j = C_j (eps_{m+2j+1} a_{m+2j} + eps_{m+2j+2} a_{m+2j+2}) and o_j = C_j
-// a_{m+2j+1} the sum is E = sum_j e_j q_j plus x times O = sum_j o_j q_j.
-// Analysis sums S_j = sum q_j D+ and T_j = sum q_j x D- over the rings and
-// forms a_{m+2j} = C_j eps S_j + C_{j-1} eps S_{j-1}, a_{m+2j+1} = C_j T_j.
-// A (ring pair, two l) costs 6 FP64 operations instead of the 8 of the
-// one-step recurrence, and its rounding errors were smaller as well (lmax
-// 1024, HEALPix: 1.3e-14 against 2.4e-14 relative RMS of the recurrence alone).
+// lambda_lm = c_lm q_l with q_l = alpha_l x q_{l-1} - q_{l-2}; the factors c_lm
+// go into a_lm.  The recurrence runs in pairs of degrees, l = m + 2j and the
+// next, on p_j = q_{m+2j} and r_j = q_{m+2j+1} / x (that of an odd degree is x
+// times a polynomial in x^2):
+//   p_j = alpha_{m+2j} x^2 r_{j-1} - p_{j-1},   r_j = alpha_{m+2j+1} p_j - r_{j-1},
+// three operations for two degrees.  Synthesis is E = sum_j c a_{m+2j} p_j plus
+// x times O = sum_j c a_{m+2j+1} r_j; analysis sums p_j D+ and r_j x D- over the
+// rings.  A (ring pair, two l) costs 7 FP64 operations instead of 8 with x
+// multiplied in each step.  The three-term recurrence in x^2 of the odd degrees
+// alone (Ishioka, J. Meteorol. Soc. Japan 96, 2018) needs 6, but gets the even
+// degrees from the difference of two values that are up to l times as large
+// next to the equator: 1e-13 on the rings there at lmax 1024 where this form has
+// 1e-15, and no gain elsewhere, as the rounding of the argument x^2 dominates
+// both (1.5e-14 at 20 degrees from a pole, against 4.3e-14 with x rounded in
+// each step).  For the slots next to a pole x^2 is 1 - sin^2 (GeomPlan::npolar).
 //
 // One recurrence serves a ring and its mirror image (x -> -x): the even part
 // E is the same and the odd part x O changes sign.
@@ -30,9 +29,9 @@
 // Underflow near the poles (Sec. 2.1 asks for rescaling and leaves the
 // algorithm to its references).  Once per plan, k_leg_start runs every
 // (m, slot) recurrence from its seed with exponent tracking (a value held as
-// q * 2^(600 sc), sc <= 0) until |q| first reaches 2^-100, and stores the j
-// that opens the block of kStartJ steps holding that step, with the two
-// recurrence values before it.  The transform kernels start each slot there:
+// value * 2^(600 sc), sc <= 0) until |p_j| or |r_j| first reaches 2^-100, and
+// stores the j that opens the block of kStartJ steps holding that step, with
+// (p_{j-1}, r_{j-1}) before it.  The transform kernels start each slot there:
 // every term they leave out has |lambda| < 2.3 * 2^-100, and from its start
 // on a slot's values stay in normal double range, so the hot loops have no
 // rescaling.  A slot whose values stay below 2^-100 up to lmax is not started.
@@ -58,14 +57,26 @@ namespace {
 
 constexpr double kDown = 0x1p-600;   // 2^-kScaleBits
 constexpr double kThresh = 0x1p-60;  // carrier bound that triggers rescaling
-constexpr double kStart = 0x1p-100;  // a slot starts once |q| reaches this
+constexpr double kStart = 0x1p-100;  // a slot starts once |p| or |r| reaches this
 static_assert(kScaleBits == 600, "kDown must equal 2^-kScaleBits");
 
-// q_0 = (-1)^m f_m s^m as carrier * 2^(600 sc), f_m = mu_m sqrt(2m+3).  s^m by
+// One pair of degrees: p, r from their predecessors, ae = alpha_{m+2j}, ao =
+// alpha_{m+2j+1}.  POLAR: x^2 is h + w (GeomPlan::npolar), else w; a slot with
+// h = 0 has the same bits in both forms.
+template <bool POLAR>
+__device__ __forceinline__ void pair_step(double ae, double ao, double w, double h, double &p, double &r) {
+    double t = w * r;
+    if (POLAR) t = fma(h, r, t);
+    p = fma(ae, t, -p);
+    r = fma(ao, p, -r);
+}
+__device__ __forceinline__ double polar_h(int slot, int npolar) { return slot < npolar ? 1.0 : 0.0; }
+
+// p_0 = (-1)^m mu_m s^m as carrier * 2^(600 sc).  s^m by
 // binary powering with frexp renormalisation; s and its squares are carried as
 // two doubles, since each squaring doubles the relative error of what it
 // squares (with one double the seed of m would be off by about m/2 roundings).
-__device__ __forceinline__ double seed_carrier(int m, double2 s, double f_m, int &sc) {
+__device__ __forceinline__ double seed_carrier(int m, double2 s, double mu_m, int &sc) {
     int eb;
     double b = frexp(s.x, &eb), bl = ldexp(s.y, -eb);
     double r = 1.0, rl = 0.0;
@@ -88,7 +99,7 @@ __device__ __forceinline__ double seed_carrier(int m, double2 s, double f_m, int
             eb = 2 * eb + e2;
         }
     }
-    const double v = ((m & 1) ? -f_m : f_m) * (r + rl);
+    const double v = ((m & 1) ? -mu_m : mu_m) * (r + rl);
     if (v == 0.0) {
         sc = 0;
         return 0.0;
@@ -101,12 +112,10 @@ __device__ __forceinline__ double seed_carrier(int m, double2 s, double f_m, int
 
 // Plan kernel: one thread per (m, slot); grid.x covers slots, grid.y = m.
 // Writes jstart[m * nslots + slot] (kNeverJ when never reached) and
-// state[m * nslots + slot] = (q_{j-2}, q_{j-1}) before step j = jstart.
+// state[m * nslots + slot] = (p_{j-1}, r_{j-1}) before step j = jstart.
 __global__ __launch_bounds__(kBlock) void k_leg_start(int lmax, int nslots, int npolar,
-                                                      const double *__restrict__ ra,
-                                                      const double *__restrict__ rb,
-                                                      const double *__restrict__ rbp,
-                                                      const double *__restrict__ seeds,
+                                                      const double *__restrict__ alpha,
+                                                      const double *__restrict__ mu,
                                                       const double *__restrict__ sw,
                                                       const double2 *__restrict__ ss,
                                                       int32_t *__restrict__ jstart,
@@ -115,28 +124,27 @@ __global__ __launch_bounds__(kBlock) void k_leg_start(int lmax, int nslots, int 
     const int m = blockIdx.y;
     if (slot >= nslots) return;
     const double w = sw[slot];
-    const int64_t jb = jcol_base(lmax, m);
-    const double *__restrict__ ca = ra + jb, *__restrict__ cb = (slot < npolar ? rbp : rb) + jb;
+    const double h = polar_h(slot, npolar);
+    const double *__restrict__ al = alpha + (int64_t)m * (2 * lmax + 1 - m) / 2 + m;
     const int nj = jcol_len(lmax, m);
     int sc;
-    const double seed = seed_carrier(m, ss[slot], seeds[m], sc);
-    // (q_{j-2}, q_{j-1}) before step j; (-seed, 0) makes step j = 0 yield the seed
-    double q2 = -seed, q1 = 0.0;
+    const double seed = seed_carrier(m, ss[slot], mu[m], sc);
+    // before step j = 0 (-seed, 0) makes that step yield the seed (alpha_m = 0)
+    double p = -seed, r = 0.0;
     int found = kNeverJ;
-    double s2 = 0.0, s1 = 0.0;
+    double sp = 0.0, sr = 0.0;
     for (int j0 = 0; j0 < nj && found == kNeverJ; j0 += kStartJ) {
-        const double b2 = q2, b1 = q1;
+        const double bp = p, br = r;
         const int bsc = sc;
         bool hit = false;
         for (int i = 0; i < kStartJ && j0 + i < nj; ++i) {
-            const double q = fma(fma(ca[j0 + i], w, cb[j0 + i]), q1, -q2);
-            q2 = q1;
-            q1 = q;
-            hit |= (sc == 0 && fabs(q) >= kStart);
-            // one step grows a value by less than 2^16 (A_j < 2 m)
-            if ((i & 1) && sc < 0 && fabs(q1) > kThresh) {
-                q1 *= kDown;
-                q2 *= kDown;
+            // the odd degree past lmax (of the last j) reads the next column or the padding: not used
+            pair_step<true>(al[2 * (j0 + i)], al[2 * (j0 + i) + 1], w, h, p, r);
+            hit |= (sc == 0 && (fabs(p) >= kStart || (fabs(r) >= kStart && m + 2 * (j0 + i) < lmax)));
+            // one step grows a value by less than 2^18 (alpha_l < 2^9)
+            if (sc < 0 && fmax(fabs(p), fabs(r)) > kThresh) {
+                p *= kDown;
+                r *= kDown;
                 ++sc;
             }
         }
@@ -144,56 +152,25 @@ __global__ __launch_bounds__(kBlock) void k_leg_start(int lmax, int nslots, int 
             found = j0;
             // a value leaves sc < 0 near 2^-660 and cannot grow past 2^-100
             // within one block, so bsc is 0 here in practice
-            s2 = ldexp(b2, kScaleBits * bsc);
-            s1 = ldexp(b1, kScaleBits * bsc);
+            sp = ldexp(bp, kScaleBits * bsc);
+            sr = ldexp(br, kScaleBits * bsc);
         }
     }
     jstart[(int64_t)m * nslots + slot] = found;
-    state[(int64_t)m * nslots + slot] = make_double2(s2, s1);
+    state[(int64_t)m * nslots + slot] = make_double2(sp, sr);
 }
 
-// Scaled coefficients of one column: entries m + 2j and m + 2j + 1 of the
-// packed column become e_j and o_j (as many entries as a_lm has: o_j exists
-// where m + 2j + 1 <= lmax).  col and out point to entry l = 0 of the column.
-__device__ __forceinline__ void prescale_column(int lmax, int m, const double2 *__restrict__ col, ParityFac f,
-                                                double2 *__restrict__ out) {
-    const int64_t jb = jcol_base(lmax, m);
-    const int nj = jcol_len(lmax, m);
-    for (int j = threadIdx.x; j < nj; j += kBlock) {
-        const int l = m + 2 * j;
-        const double p1 = f.pe1[jb + j], p2 = f.pe2[jb + j], po = f.po[jb + j];
-        const double2 a0 = col[l];
-        const double2 a1 = l + 1 <= lmax ? col[l + 1] : make_double2(0.0, 0.0);
-        const double2 a2 = l + 2 <= lmax ? col[l + 2] : make_double2(0.0, 0.0);
-        // m = 0: Im a_l0 is ignored
-        out[l] = make_double2(fma(p1, a0.x, p2 * a2.x), m == 0 ? 0.0 : fma(p1, a0.y, p2 * a2.y));
-        if (l + 1 <= lmax) out[l + 1] = make_double2(po * a1.x, m == 0 ? 0.0 : po * a1.y);
-    }
-}
-// grid.x = m, grid.y = map
-__global__ __launch_bounds__(kBlock) void k_prescale(int64_t nalm, int lmax, const double2 *__restrict__ alm,
-                                                     ParityFac f, double2 *__restrict__ out) {
-    const int m = blockIdx.x;
-    const int64_t at = blockIdx.y * nalm + (int64_t)m * (2 * lmax + 1 - m) / 2;
-    prescale_column(lmax, m, alm + at, f, out + at);
-}
-
-// a_lm of one column from the sums over the rings, given by sum(l): S_j at
-// l = m + 2j and T_j at l = m + 2j + 1.
-template <class Sum>
-__device__ __forceinline__ void finish_column(int lmax, int m, ParityFac f, Sum sum, double2 *__restrict__ col) {
-    const int64_t jb = jcol_base(lmax, m);
-    for (int l = m + threadIdx.x; l <= lmax; l += kBlock) {
-        const int j = (l - m) >> 1;
-        const double2 v = sum(l);
-        if ((l - m) & 1) {
-            const double c = f.po[jb + j];
-            col[l] = make_double2(c * v.x, m == 0 ? 0.0 : c * v.y);
-        } else {
-            const double c = f.pe1[jb + j], d = j > 0 ? f.pe2[jb + j - 1] : 0.0;
-            const double2 u = j > 0 ? sum(l - 2) : make_double2(0.0, 0.0);
-            col[l] = make_double2(fma(c, v.x, d * u.x), m == 0 ? 0.0 : fma(c, v.y, d * u.y));
-        }
+__global__ __launch_bounds__(kBlock) void k_prescale(int64_t nalm, int lmax, int nmaps,
+                                                     const double2 *__restrict__ alm,
+                                                     const double *__restrict__ cfac,
+                                                     double2 *__restrict__ out) {
+    const int64_t total = nalm * nmaps;
+    for (int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x; i < total; i += (int64_t)gridDim.x * kBlock) {
+        const int64_t k = i % nalm;
+        const double c = cfac[k];
+        const double2 a = alm[i];
+        // entries k <= lmax are m = 0: Im a_l0 is ignored
+        out[i] = make_double2(a.x * c, k <= lmax ? 0.0 : a.y * c);
     }
 }
 
@@ -203,25 +180,24 @@ __device__ __forceinline__ void finish_column(int lmax, int m, ParityFac f, Sum 
 // skipped whole, and table reads are contiguous: 2 to 5 % at HEALPix 512 to
 // 700), for maps map0 .. map0 + M - 1 (those past nmaps repeat the last map and are not
 // stored).  Each recurrence value serves the M maps, so a slot and two l cost
-// 2 + 4M operations instead of 6M; per map the arithmetic (the same fused
+// 3 + 4M operations instead of 7M; per map the arithmetic (the same fused
 // multiply-adds in the same order) does not depend on M, so results are the
 // same bits for any M.  The wave works on its own (no cross-wave step), so a
 // tile may be one wave's (li = lane) or a workgroup's (li = thread index).
-template <int T, int M = 1>
-__device__ __forceinline__ void syn_tile(const SynArgs &A, int m, int map0, int nmaps, int slot0, int li) {
+// POLAR: the wave may hold polar slots.
+template <int T, int M, bool POLAR>
+__device__ __forceinline__ void syn_wave(const SynArgs &A, int m, int map0, int nmaps, int wave0) {
+    constexpr std::integral_constant<bool, POLAR> polar{};
     const int lmax = A.lmax, mmax = A.mmax, nslots = A.nslots, nrings = A.nrings;
     const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2;  // (l, m) lives at base + l
     ConstC a[M];
 #pragma unroll
     for (int k = 0; k < M; ++k) a[k] = ro(A.ap + (int64_t)min(map0 + k, nmaps - 1) * A.nalm + base + m);
-    // the wave's slots are all polar or all not (npolar is a multiple of the tile)
-    const int wave0 = __builtin_amdgcn_readfirstlane(slot0 + (li & ~63) * T), lane = li & 63;
-    const bool polar = wave0 < A.npolar;
-    const int64_t jb = jcol_base(lmax, m);
-    const const_ptr<double> ra = ro(A.ra + jb), rb = ro((polar ? A.rbp : A.rb) + jb);
+    const int lane = threadIdx.x & 63;
+    const const_ptr<double> al = ro(A.alpha + base + m);
     const int nj = jcol_len(lmax, m);
 
-    double w[T], q1[T], q2[T], er[T][M], ei[T][M], orr[T][M], oi[T][M];
+    double w[T], h[T], p[T], r[T], er[T][M], ei[T][M], orr[T][M], oi[T][M];
     // what the stores need is loaded with the rest where registers allow, so
     // that a short recurrence does not end on another memory round trip
     constexpr bool kEarly = T * M <= 2;
@@ -239,57 +215,51 @@ __device__ __forceinline__ void syn_tile(const SynArgs &A, int m, int map0, int 
             rs[u] = A.rsouth[sl];
         }
         w[u] = act ? A.sw[slot] : 0.0;
+        h[u] = polar_h(slot, A.npolar);
         js[u] = act ? A.jstart[(int64_t)m * nslots + slot] : kNeverJ;
         const double2 st = act ? A.state[(int64_t)m * nslots + slot] : make_double2(0.0, 0.0);
-        q2[u] = st.x;
-        q1[u] = st.y;
+        p[u] = st.x;
+        r[u] = st.y;
 #pragma unroll
         for (int k = 0; k < M; ++k) er[u][k] = ei[u][k] = orr[u][k] = oi[u][k] = 0.0;
         lo = min(lo, js[u]);
         if (js[u] < nj) hi = max(hi, js[u]);
         // not started for this lmax: the state is carried but never used
-        if (js[u] >= nj) q1[u] = q2[u] = 0.0;
+        if (js[u] >= nj) p[u] = r[u] = 0.0;
     }
     lo = wave_min(lo);
     hi = wave_max(hi);
 
     struct Coef {
-        double a, b;  // A_j and B_j (or A_j + B_j)
+        double ae, ao;  // alpha of the even and of the odd degree
         double2 e[M], o[M];
     };
     auto load = [&](int j, Coef &k) {
-        k.a = ra[j];
-        k.b = rb[j];
+        k.ae = al[2 * j];
+        k.ao = al[2 * j + 1];
 #pragma unroll
         for (int i = 0; i < M; ++i) {
             k.e[i] = a[i][2 * j];
             k.o[i] = a[i][2 * j + 1];
         }
     };
-    // step j of slot u: q_j, then its terms of both parities (ODD: o_j exists)
-    // with A_j given in a vector register (an instruction reads one scalar operand)
-    auto step = [&](const Coef &c, double aj, int u, auto odd) {
-        const double q = fma(fma(aj, w[u], c.b), q1[u], -q2[u]);
-        q2[u] = q1[u];
-        q1[u] = q;
+    // step j of slot u: p_j and r_j, then the terms of both degrees (ODD: m + 2j + 1 <= lmax)
+    auto step = [&](const Coef &c, int u, auto polar, auto odd) {
+        pair_step<decltype(polar)::value>(c.ae, c.ao, w[u], h[u], p[u], r[u]);
 #pragma unroll
         for (int k = 0; k < M; ++k) {
-            er[u][k] = fma(c.e[k].x, q, er[u][k]);
-            ei[u][k] = fma(c.e[k].y, q, ei[u][k]);
+            er[u][k] = fma(c.e[k].x, p[u], er[u][k]);
+            ei[u][k] = fma(c.e[k].y, p[u], ei[u][k]);
             if constexpr (decltype(odd)::value) {
-                orr[u][k] = fma(c.o[k].x, q, orr[u][k]);
-                oi[u][k] = fma(c.o[k].y, q, oi[u][k]);
+                orr[u][k] = fma(c.o[k].x, r[u], orr[u][k]);
+                oi[u][k] = fma(c.o[k].y, r[u], oi[u][k]);
             }
         }
-    };
-    auto vec = [](double v) {
-        asm("" : "+v"(v));
-        return v;
     };
     const int nfull = (lmax - m + 1) / 2;  // steps with both parities
 
     // Blocks of kStartJ steps of both parities, in halves of two steps with two
-    // coefficient sets in turn, each loaded one half ahead (a, ra and rb are
+    // coefficient sets in turn, each loaded one half ahead (a and alpha are
     // padded, so the loads past the column's end stay in bounds).  Start
     // positions are multiples of kStartJ: while slots join (j <= hi) the lanes
     // of a slot that has not started are masked off and it keeps its state.
@@ -298,7 +268,7 @@ __device__ __forceinline__ void syn_tile(const SynArgs &A, int m, int map0, int 
     int j = lo;
     if (j + kStartJ <= nfull) {
         // running pointers: the loads of a half are one run of scalar loads each
-        const_ptr<double> pra = ra + j, prb = rb + j;
+        const_ptr<double> pal = al + 2 * j;
         const_ptr<dvec2> pa[M];
 #pragma unroll
         for (int k = 0; k < M; ++k) pa[k] = a[k].p + 2 * j;
@@ -306,8 +276,8 @@ __device__ __forceinline__ void syn_tile(const SynArgs &A, int m, int map0, int 
         auto load2 = [&](int ofs, Coef (&c)[2]) {
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                c[i].a = pra[ofs + i];
-                c[i].b = prb[ofs + i];
+                c[i].ae = pal[2 * (ofs + i)];
+                c[i].ao = pal[2 * (ofs + i) + 1];
 #pragma unroll
                 for (int k = 0; k < M; ++k) {
                     c[i].e[k] = pair(pa[k][2 * (ofs + i)]);
@@ -319,25 +289,21 @@ __device__ __forceinline__ void syn_tile(const SynArgs &A, int m, int map0, int 
             asm volatile("" ::: "memory");
         };
         auto masked2 = [&](const Coef (&c)[2]) {
-            const double a0 = vec(c[0].a), a1 = vec(c[1].a);
 #pragma unroll
             for (int u = 0; u < T; ++u)
                 if (j >= js[u]) {
-                    step(c[0], a0, u, std::true_type{});
-                    step(c[1], a1, u, std::true_type{});
+                    step(c[0], u, polar, std::true_type{});
+                    step(c[1], u, polar, std::true_type{});
                 }
         };
         auto step2 = [&](const Coef (&c)[2]) {
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const double aj = vec(c[i].a);
+            for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int u = 0; u < T; ++u) step(c[i], aj, u, std::true_type{});
-            }
+                for (int u = 0; u < T; ++u) step(c[i], u, polar, std::true_type{});
         };
         auto advance = [&]() {
-            pra += kStartJ;
-            prb += kStartJ;
+            pal += 2 * kStartJ;
 #pragma unroll
             for (int k = 0; k < M; ++k) pa[k] += 2 * kStartJ;
         };
@@ -374,9 +340,9 @@ __device__ __forceinline__ void syn_tile(const SynArgs &A, int m, int map0, int 
         for (int u = 0; u < T; ++u)
             if (j >= js[u]) {
                 if (j < nfull)
-                    step(c, c.a, u, std::true_type{});
+                    step(c, u, polar, std::true_type{});
                 else
-                    step(c, c.a, u, std::false_type{});
+                    step(c, u, polar, std::false_type{});
             }
     }
 
@@ -401,6 +367,15 @@ __device__ __forceinline__ void syn_tile(const SynArgs &A, int m, int map0, int 
     }
 }
 
+template <int T, int M = 1>
+__device__ __forceinline__ void syn_tile(const SynArgs &A, int m, int map0, int nmaps, int slot0, int li) {
+    const int wave0 = __builtin_amdgcn_readfirstlane(slot0 + (li & ~63) * T);
+    if (wave0 < A.npolar)
+        syn_wave<T, M, true>(A, m, map0, nmaps, wave0);
+    else
+        syn_wave<T, M, false>(A, m, map0, nmaps, wave0);
+}
+
 // Synthesis of M maps per workgroup (grid.y = map group of M), T slots per
 // lane: the recurrence shared by the M maps (syn_tile).
 template <int T, int M>
@@ -411,10 +386,9 @@ __global__ __launch_bounds__(kBlock, 2) void k_leg_syn_mm(SynArgs A, int tiles, 
     const int map0 = blockIdx.y * M;
     const int64_t base = (int64_t)m * (2 * A.lmax + 1 - m) / 2;
     const double warm_a = warm_l2(reinterpret_cast<const double *>(A.ap + (int64_t)map0 * A.nalm + base), 2, m, A.lmax);
-    const double warm_al = warm_l2(A.ra + jcol_base(A.lmax, m), 1, 0, jcol_len(A.lmax, m) - 1);
-    const double warm_bl = warm_l2(A.rb + jcol_base(A.lmax, m), 1, 0, jcol_len(A.lmax, m) - 1);
+    const double warm_al = warm_l2(A.alpha + base, 1, m, A.lmax);
     syn_tile<T, M>(A, m, map0, nmaps, tile * kBlock * T, (int)threadIdx.x);
-    asm volatile("" ::"v"(warm_a), "v"(warm_al), "v"(warm_bl));  // the warming loads are waited for only here
+    asm volatile("" ::"v"(warm_a), "v"(warm_al));  // the warming loads are waited for only here
 }
 
 // Synthesis kernel: grid.x = (m, 256T-slot tile) in the XCD-aware order,
@@ -427,14 +401,13 @@ __global__ __launch_bounds__(kBlock, 4) void k_leg_syn(SynArgs A, int tiles) {
     const int64_t base = (int64_t)m * (2 * A.lmax + 1 - m) / 2;
     const double warm_a = warm_l2(reinterpret_cast<const double *>(A.ap + (int64_t)blockIdx.y * A.nalm + base), 2,
                                   m, A.lmax);
-    const double warm_al = warm_l2(A.ra + jcol_base(A.lmax, m), 1, 0, jcol_len(A.lmax, m) - 1);
-    const double warm_bl = warm_l2(A.rb + jcol_base(A.lmax, m), 1, 0, jcol_len(A.lmax, m) - 1);
+    const double warm_al = warm_l2(A.alpha + base, 1, m, A.lmax);
     syn_tile<T>(A, m, (int)blockIdx.y, (int)gridDim.y, tile * kBlock * T, (int)threadIdx.x);
-    asm volatile("" ::"v"(warm_a), "v"(warm_al), "v"(warm_bl));  // the warming loads are waited for only here
+    asm volatile("" ::"v"(warm_a), "v"(warm_al));  // the warming loads are waited for only here
 }
 
-constexpr int kChunk = kStartJ;       // recurrence steps per in-wave reduction in analysis
-constexpr int kVals = 4 * kChunk;     // sums per chunk: (step, {S re, S im, T re, T im})
+constexpr int kChunk = kStartJ;       // recurrence steps (two degrees each) per in-wave reduction in analysis
+constexpr int kVals = 4 * kChunk;     // sums per chunk: (step, {even re, even im, odd re, odd im})
 // chunks between cross-wave flushes (one barrier each)
 constexpr int kFlush = 8;
 // Wave-private rows of the in-wave reduction: 16 doubles and 2 of padding (the
@@ -442,25 +415,18 @@ constexpr int kFlush = 8;
 constexpr int kTRow = 18;
 typedef double SumRows[kVals][kTRow];
 
-// Coefficients of one chunk (scalar registers): A_j, B_j, and for the first
-// sets of a lane's slots B_j or (polar) A_j + B_j.
+// alpha of one chunk (scalar registers)
 struct AnaCoef {
-    double a[kChunk], b[kChunk], b0[kChunk];
+    double a[2 * kChunk];
 };
 struct AnaCoefPtr {
-    const_ptr<double> a, b, b0;  // at the chunk that load() reads next
+    const_ptr<double> a;  // at the chunk that load() reads next
     // entries past the column's end belong to the next column or the padding
     // and are never used
     __device__ __forceinline__ void load(AnaCoef &c) {
 #pragma unroll
-        for (int i = 0; i < kChunk; ++i) {
-            c.a[i] = a[i];
-            c.b[i] = b[i];
-            c.b0[i] = b0[i];
-        }
-        a += kChunk;
-        b += kChunk;
-        b0 += kChunk;
+        for (int i = 0; i < 2 * kChunk; ++i) c.a[i] = a[i];
+        a += 2 * kChunk;
         // compiler-only fence: the loads stay here, ahead of the work that hides them
         asm volatile("" ::: "memory");
     }
@@ -484,9 +450,8 @@ constexpr int kAnaWaves = kAnaThreads / 64;
 // per-wave chunk sums awaiting a cross-wave flush, and the waves' first starts.
 template <int W = kAnaWaves>
 struct AnaLds {
-    alignas(16) SumRows tbuf[W][2];
+    alignas(16) SumRows tbuf[W];
     double ring[2][kFlush][W][kVals];
-    double carry[2][2];  // S_{j-1} before a flush's first step
     int wstart[W];
     static_assert(kFlush * kVals <= 64 * W, "one thread per flushed value");
 };
@@ -494,9 +459,11 @@ struct AnaLds {
 // The slot operands of one lane, slots slot0 + stride t + lane (t < T, sets of
 // 64 slots): recurrence argument, start, recurrence state and the pair sums
 // D+ = north + south and x D-, D- = north - south, of Delta_m.
-template <int T>
+// The first PS sets may hold polar slots.
+template <int T, int PS>
 struct AnaSlots {
-    double w[T], q1[T], q2[T], pr[T], pi[T], mr[T], mi[T];
+    static constexpr int kPolar = PS < T ? PS : T;
+    double w[T], h[kPolar], p[T], r[T], pr[T], pi[T], mr[T], mi[T];
     int js[T];
     int lo;  // wave-uniform: earliest start (kNeverJ if none)
 
@@ -513,14 +480,15 @@ struct AnaSlots {
             const bool act = slot < nslots;
             const int sl = act ? slot : nslots - 1;
             w[t] = A.sw[sl];
+            if (t < PS) h[t < PS ? t : 0] = polar_h(slot, A.npolar);
             x[t] = A.sx[sl];
             rn[t] = A.rn[sl];
             rs[t] = A.rsouth[sl];
             const int js0 = A.jstart[(int64_t)m * nslots + sl];
             const double2 st = A.state[(int64_t)m * nslots + sl];
             js[t] = act && js0 < nj ? js0 : kNeverJ;
-            q2[t] = st.x;
-            q1[t] = st.y;
+            p[t] = st.x;
+            r[t] = st.y;
         }
         lo = kNeverJ;
 #pragma unroll
@@ -538,36 +506,26 @@ struct AnaSlots {
         }
         lo = wave_min(lo);
     }
-    // One chunk of kChunk recurrence steps from j0 on: acc = sum over the
-    // slots of q_j * (D+, x D-) per step.  A slot that has not started keeps its
+    // One chunk of kChunk recurrence steps from j0 on: acc = sums over the slots
+    // of p_j D+ and r_j x D- per step.  A slot that has not started keeps its
     // state (its lanes masked off; a set that has not started at all is skipped).
-    // FULL: no end-of-column guard (nsteps steps otherwise).  The first PS sets
-    // take c.b0 (they may be polar), the others c.b.
-    template <bool FULL, int PS>
-    __device__ __forceinline__ void chunk(int j0, int nsteps, const AnaCoef &c, double (&acc)[kVals]) {
+    // Steps and degrees past lmax give sums that nobody stores.
+    __device__ __forceinline__ void chunk(int j0, const AnaCoef &c, double (&acc)[kVals]) {
 #pragma unroll
         for (int v = 0; v < kVals; ++v) acc[v] = 0.0;
-        // A_j in vector registers: an instruction reads one scalar operand, B_j
-        double a[kChunk];
-#pragma unroll
-        for (int i = 0; i < kChunk; ++i) {
-            a[i] = c.a[i];
-            asm("" : "+v"(a[i]));
-        }
 #pragma unroll
         for (int t = T - 1; t >= 0; --t) {
             if (j0 >= js[t]) {
 #pragma unroll
                 for (int i = 0; i < kChunk; ++i) {
-                    if (FULL || i < nsteps) {
-                        const double q = fma(fma(a[i], w[t], t >= PS ? c.b[i] : c.b0[i]), q1[t], -q2[t]);
-                        q2[t] = q1[t];
-                        q1[t] = q;
-                        acc[4 * i + 0] = fma(q, pr[t], acc[4 * i + 0]);
-                        acc[4 * i + 1] = fma(q, pi[t], acc[4 * i + 1]);
-                        acc[4 * i + 2] = fma(q, mr[t], acc[4 * i + 2]);
-                        acc[4 * i + 3] = fma(q, mi[t], acc[4 * i + 3]);
-                    }
+                    if (t < PS)
+                        pair_step<true>(c.a[2 * i], c.a[2 * i + 1], w[t], h[t < PS ? t : 0], p[t], r[t]);
+                    else
+                        pair_step<false>(c.a[2 * i], c.a[2 * i + 1], w[t], 0.0, p[t], r[t]);
+                    acc[4 * i + 0] = fma(p[t], pr[t], acc[4 * i + 0]);
+                    acc[4 * i + 1] = fma(p[t], pi[t], acc[4 * i + 1]);
+                    acc[4 * i + 2] = fma(r[t], mr[t], acc[4 * i + 2]);
+                    acc[4 * i + 3] = fma(r[t], mi[t], acc[4 * i + 3]);
                 }
             }
         }
@@ -619,13 +577,13 @@ __device__ __forceinline__ double wave_sum16(SumRows &tb, const double (&acc)[kV
     return v;
 }
 
-// Brings the factors of one column that an analysis reads at the end of its
-// chunks into this XCD's L2.
+// Brings the factors c_lm of one column that an analysis reads at the end of
+// its chunks into this XCD's L2.
 template <int NT>
-__device__ __forceinline__ void warm_factors(const ParityFac &f, int64_t jb, int nj) {
-    for (int i = 16 * (int)threadIdx.x; i < nj; i += 16 * NT) {
-        const double a = f.pe1[jb + i], b = f.pe2[jb + i], c = f.po[jb + i];
-        asm volatile("" ::"v"(a), "v"(b), "v"(c));
+__device__ __forceinline__ void warm_factors(const double *cfac, int n) {
+    for (int i = 16 * (int)threadIdx.x; i < n; i += 16 * NT) {
+        const double a = cfac[i];
+        asm volatile("" ::"v"(a));
     }
 }
 
@@ -637,29 +595,25 @@ __device__ __forceinline__ void warm_factors(const ParityFac &f, int64_t jb, int
 // are added in wave order after one barrier.  The workgroup starts at the
 // earliest start of its slots (a_lm before it get no term).  With one group
 // the finished a_lm are written; otherwise the group's sums go to part[(map *
-// groups + group) * nalm + idx] for k_ana_finish.  Every thread of the
+// groups + group) * nalm + idx] for k_ana_combine.  Every thread of the
 // workgroup must call it.
 template <int T, int W = kAnaWaves>
 __device__ __forceinline__ void ana_group(const AnaArgs &A, int m, int grp, int map, int groups, AnaLds<W> &L) {
     constexpr int kThreads = 64 * W;
     const int lmax = A.lmax, nj = jcol_len(lmax, m);
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2, jb = jcol_base(lmax, m);
+    const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2;
     const double2 *__restrict__ d = A.delta + (int64_t)map * A.nrings * (A.mmax + 1);
     double2 *__restrict__ dst = (groups == 1) ? A.alm + (int64_t)map * A.nalm + base
                                               : A.part + ((int64_t)map * groups + grp) * A.nalm + base;
-    // the first sets of the first group hold the polar slots, if any
-    constexpr int PS = kPolarSlots / kThreads;
-    static_assert(PS * kThreads == kPolarSlots, "whole sets of polar slots");
-    const double *b0 = grp == 0 && A.npolar ? A.rbp : A.rb;
     // this column's coefficients into the XCD's L2 while the slots are loaded
-    const double warm_a = warm_l2(A.ra + jb, 1, 0, nj - 1), warm_b = warm_l2(A.rb + jb, 1, 0, nj - 1);
-    AnaSlots<T> S;
+    const double warm_al = warm_l2(A.alpha + base, 1, m, lmax);
+    AnaSlots<T, kMaxPolar / kThreads> S;  // polar slots: the first sets of the first group
+    static_assert(kMaxPolar % kThreads == 0, "whole sets of polar slots");
     S.load(A, m, d, grp * kThreads * T + wave * 64, kThreads);
-    asm volatile("" ::"v"(warm_a), "v"(warm_b));
-    if (groups == 1) warm_factors<kThreads>(A.fac, jb, nj);
+    asm volatile("" ::"v"(warm_al));
+    if (groups == 1) warm_factors<kThreads>(A.cfac + base + m, lmax - m + 1);
     if (lane == 0) L.wstart[wave] = S.lo;
-    if (tid < 4) L.carry[tid >> 1][tid & 1] = 0.0;
     __syncthreads();
     int j0s = nj;
 #pragma unroll
@@ -669,52 +623,36 @@ __device__ __forceinline__ void ana_group(const AnaArgs &A, int m, int grp, int 
     for (int l = m + tid; l < m + 2 * j0s && l <= lmax; l += kThreads) dst[l] = make_double2(0.0, 0.0);
 
     // Every kFlush chunks (or at the last): thread f < nchunks*kVals takes the
-    // value (chunk f/kVals, v = f%kVals) of the W waves' sums and writes it.
+    // value (chunk f/kVals, f%kVals) of the W waves' sums and writes it.
     auto flush = [&](int jbase, int par, int nchunks) {
         const int fk = tid / kVals, fv = tid % kVals, fc = tid & 3;
-        const int j = jbase + (tid >> 2), l = m + 2 * j + (fc >> 1);
-        const bool mine = tid < nchunks * kVals;
-        double f0 = 0.0, f1 = 0.0;  // loaded ahead of the barrier
-        if (groups == 1 && mine && j < nj) {
-            f0 = fc < 2 ? A.fac.pe1[jb + j] : A.fac.po[jb + j];
-            if (fc < 2 && j > 0) f1 = A.fac.pe2[jb + j - 1];
-        }
+        const int l = m + 2 * (jbase + (tid >> 2)) + (fc >> 1);
+        const bool mine = tid < nchunks * kVals && l <= lmax;
+        const double c = groups == 1 && mine ? A.cfac[base + l] : 1.0;  // loaded ahead of the barrier
         __syncthreads();
         if (mine) {
-            auto total = [&](int chunk, int v) {
-                double t = 0.0;
+            double v = 0.0;
 #pragma unroll
-                for (int u = 0; u < W; ++u) t += L.ring[par][chunk][u][v];
-                return t;
-            };
-            double v = total(fk, fv);
-            if (groups == 1) {
-                if (fc < 2) {  // even degree: S_j and S_{j-1}
-                    const double before = fv >= 4 ? total(fk, fv - 4) : fk > 0 ? total(fk - 1, fv + 12) : L.carry[par][fc];
-                    if (fk == kFlush - 1 && fv >= kVals - 4) L.carry[par ^ 1][fc] = v;
-                    v = fma(f0, v, f1 * before);
-                } else {
-                    v *= f0;
-                }
-                if (m == 0 && (fc & 1)) v = 0.0;
-            }
-            if (l <= lmax) reinterpret_cast<double *>(dst + l)[fc & 1] = v;
+            for (int u = 0; u < W; ++u) v += L.ring[par][fk][u][fv];
+            if (groups == 1) v = m == 0 && (fc & 1) ? 0.0 : v * c;
+            reinterpret_cast<double *>(dst + l)[fc & 1] = v;
         }
     };
 
     // the next chunk's coefficients are loaded at the start of a chunk, so that
     // they arrive under its arithmetic; the waits for the LDS traffic that
     // follows then find them there
-    AnaCoefPtr cp{ro(A.ra + jb + j0s), ro(A.rb + jb + j0s), ro(b0 + jb + j0s)};
-    static_assert(2 * kChunk <= kCoefPad, "coefficient padding too short");
+    AnaCoefPtr cp{ro(A.alpha + base + m + 2 * j0s)};
+    static_assert(4 * kChunk <= kCoefPad, "coefficient padding too short");
     AnaCoef cur, nxt;
     cp.load(cur);
     int par = 0, kc = 0, jbase = j0s;
-    auto one = [&](int j0, auto full) {
+#pragma unroll 1
+    for (int j0 = j0s; j0 < nj; j0 += kChunk) {
         cp.load(nxt);
         double acc[kVals];
-        S.template chunk<decltype(full)::value, PS>(j0, nj - j0, cur, acc);
-        const double v = wave_sum16(L.tbuf[wave][0], acc);
+        S.chunk(j0, cur, acc);
+        const double v = wave_sum16(L.tbuf[wave], acc);
         if ((lane & 3) == 0) L.ring[par][kc][wave][lane >> 2] = v;
         cur = nxt;
         if (++kc == kFlush || j0 + kChunk >= nj) {
@@ -723,87 +661,55 @@ __device__ __forceinline__ void ana_group(const AnaArgs &A, int m, int grp, int 
             par ^= 1;
             kc = 0;
         }
-    };
-    int j0 = j0s;
-#pragma unroll 1
-    for (; j0 + kChunk <= nj; j0 += kChunk) one(j0, std::true_type{});
-    if (j0 < nj) one(j0, std::false_type{});  // the ragged last chunk
+    }
 }
 
 // Analysis of one m of one map by one wave holding every slot (nslots <=
 // 64 T; lane i owns slots 64 t + i): per chunk the wave's sums go straight
 // to a_lm, with no step across waves, so the waves of a workgroup may each
-// work on their own m.  tb: the wave's reduction rows, two sets in turn.
+// work on their own m.  tb: the wave's reduction rows.
 template <int T>
-__device__ __forceinline__ void ana_wave(const AnaArgs &A, int m, int map, SumRows (&tb)[2]) {
+__device__ __forceinline__ void ana_wave(const AnaArgs &A, int m, int map, SumRows &tb) {
     const int lmax = A.lmax, nj = jcol_len(lmax, m);
     const int lane = threadIdx.x & 63;
-    const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2, jb = jcol_base(lmax, m);
+    const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2;
     const double2 *__restrict__ d = A.delta + (int64_t)map * A.nrings * (A.mmax + 1);
     double2 *__restrict__ dst = A.alm + (int64_t)map * A.nalm + base;
-    const int warm = min(16 * lane, nj - 1);  // the column's coefficients into L2, as warm_l2
-    const double warm_a = A.ra[jb + warm], warm_b = A.rb[jb + warm];
-    AnaSlots<T> S;
+    const double warm_al = A.alpha[base + min(m + 16 * lane, lmax)];  // the column into L2, as warm_l2
+    AnaSlots<T, kMaxPolar / 64> S;
     S.load(A, m, d, 0, 64);
-    asm volatile("" ::"v"(warm_a), "v"(warm_b));
+    asm volatile("" ::"v"(warm_al));
     const int lo = S.lo;
     for (int l = m + lane; l < m + 2 * min(lo, nj) && l <= lmax; l += 64) dst[l] = make_double2(0.0, 0.0);
     if (lo >= nj) return;
-    const double *b0 = A.npolar ? A.rbp : A.rb;
-    AnaCoefPtr cp{ro(A.ra + jb + lo), ro(A.rb + jb + lo), ro(b0 + jb + lo)};
+    AnaCoefPtr cp{ro(A.alpha + base + m + 2 * lo)};
     AnaCoef cur, nxt;
     cp.load(cur);
-    const int fv = lane >> 2, fc = fv & 3;
-    // before the first chunk S_{j-1} is zero: rows 12 .. 15 of the set that chunk reads
-    if (lane < 16) {
-#pragma unroll
-        for (int v = kVals - 4; v < kVals; ++v) tb[1][v][lane] = 0.0;
-    }
-    int set = 0;
-    // the factors of a chunk are loaded one chunk ahead
-    auto factors = [&](int j0) {
-        const int j = j0 + (fv >> 2);
-        double2 f = make_double2(0.0, 0.0);
-        if (j < nj) {
-            f.x = fc < 2 ? A.fac.pe1[jb + j] : A.fac.po[jb + j];
-            if (fc < 2 && j > 0) f.y = A.fac.pe2[jb + j - 1];
-        }
-        return f;
-    };
-    double2 fac = factors(lo);
-    auto one = [&](int j0, auto full) {
-        cp.load(nxt);
-        double2 fac_next = factors(j0 + kChunk);
-        double acc[kVals];
-        S.template chunk<decltype(full)::value, kPolarSlots / 64>(j0, nj - j0, cur, acc);
-        // S_j of this lane's column and S_{j-1}: rows v and v - 4, the latter for
-        // the chunk's first step from the previous chunk's rows (both sums run
-        // side by side; passing one on between lanes would lengthen the chain)
-        sum_to_rows(tb[set], acc);
-        const double v = sum_row(tb[set][fv]), before = sum_row(fv >= 4 ? tb[set][fv - 4] : tb[set ^ 1][fv + 12]);
-        __builtin_amdgcn_wave_barrier();
-        set ^= 1;
-        cur = nxt;
-        // the next factors are waited for here: behind the store the wait would
-        // include the store's own way to memory, in every chunk
-        asm volatile("" : "+v"(fac_next.x), "+v"(fac_next.y));
-        const int l = m + 2 * (j0 + (fv >> 2)) + (fc >> 1);
-        if ((lane & 3) == 0 && l <= lmax) {
-            const double r = fc < 2 ? fma(fac.x, v, fac.y * before) : fac.x * v;
-            reinterpret_cast<double *>(dst + l)[fc & 1] = (m == 0 && (fc & 1)) ? 0.0 : r;
-        }
-        fac = fac_next;
-    };
-    int j0 = lo;
+    // this lane's value of a chunk: degree offset and part; its factor is loaded one chunk ahead
+    const int fv = lane >> 2, fc = fv & 3, dl = 2 * (fv >> 2) + (fc >> 1);
+    auto factor = [&](int j0) { return A.cfac[base + min(m + 2 * j0 + dl, lmax)]; };
+    double fac = factor(lo);
 #pragma unroll 1
-    for (; j0 + kChunk <= nj; j0 += kChunk) one(j0, std::true_type{});
-    if (j0 < nj) one(j0, std::false_type{});
+    for (int j0 = lo; j0 < nj; j0 += kChunk) {
+        cp.load(nxt);
+        double fac_next = factor(j0 + kChunk);
+        double acc[kVals];
+        S.chunk(j0, cur, acc);
+        const double v = wave_sum16(tb, acc);
+        cur = nxt;
+        // the next factor is waited for here: behind the store the wait would
+        // include the store's own way to memory, in every chunk
+        asm volatile("" : "+v"(fac_next));
+        const int l = m + 2 * j0 + dl;
+        if ((lane & 3) == 0 && l <= lmax)
+            reinterpret_cast<double *>(dst + l)[fc & 1] = (m == 0 && (fc & 1)) ? 0.0 : v * fac;
+        fac = fac_next;
+    }
 }
 
 // Analysis kernel: grid.x = (m, slot group) in the XCD-aware order, grid.y =
-// map.  Three waves per SIMD at 8 slots per lane (168 VGPRs, 7 of them spilled
-// outside the chunk loop) run faster than two without the spills: 589 against
-// 637 us at HEALPix 1024 / lmax 2048.
+// map.  Three waves per SIMD at 8 slots per lane (166 VGPRs): 549 us at HEALPix
+// 1024 / lmax 2048 (two waves, with a recurrence of 6 operations: 637 against 589).
 template <int T, int W>
 __global__ __launch_bounds__(64 * W, T <= 4 ? 4 : 3) void k_leg_ana(AnaArgs A, int groups) {
     __shared__ AnaLds<W> L;
@@ -813,14 +719,13 @@ __global__ __launch_bounds__(64 * W, T <= 4 ? 4 : 3) void k_leg_ana(AnaArgs A, i
 }
 // At most 64 slots, one wave per m: grid.x = m in the XCD-aware order, grid.y = map.
 __global__ __launch_bounds__(64) void k_leg_ana_wave(AnaArgs A) {
-    __shared__ alignas(16) SumRows tb[2];
+    __shared__ alignas(16) SumRows tb;
     const MPart mp = xcd_m_part(1);
     if (mp.m > A.mmax) return;
     ana_wave<1>(A, mp.m, (int)blockIdx.y, tb);
 }
 
-// FP64 analysis with several groups: the sums S_j, T_j of a column are
-// part[map][g][idx] added over the groups in order (sum), then a_lm.
+// Sum of the groups' partial a_lm, groups in order.
 __device__ __forceinline__ double2 group_sum(const double2 *__restrict__ part, int64_t nalm, int groups, int64_t idx) {
     double sr = 0.0, si = 0.0;
     for (int g = 0; g < groups; ++g) {
@@ -830,17 +735,7 @@ __device__ __forceinline__ double2 group_sum(const double2 *__restrict__ part, i
     }
     return make_double2(sr, si);
 }
-// grid.x = m, grid.y = map
-__global__ __launch_bounds__(kBlock) void k_ana_finish(int64_t nalm, int lmax, int groups,
-                                                       const double2 *__restrict__ part, ParityFac f,
-                                                       double2 *__restrict__ alm) {
-    const int m = blockIdx.x;
-    const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2, map = blockIdx.y;
-    const double2 *__restrict__ src = part + map * groups * nalm;
-    finish_column(lmax, m, f, [&](int l) { return group_sum(src, nalm, groups, base + l); }, alm + map * nalm + base);
-}
-
-// Mixed analysis: a_lm = c_lm * sum_{g < groups} part[map][g][idx], groups summed in order.
+// a_lm = c_lm * sum_{g < groups} part[map][g][idx], groups summed in order.
 __global__ __launch_bounds__(kBlock) void k_ana_combine(int64_t nalm, int lmax, int nmaps, int groups,
                                                         const double2 *__restrict__ part,
                                                         const double *__restrict__ cfac,
@@ -907,27 +802,33 @@ __global__ __launch_bounds__(kBlock, 3) void k_leg_batch(const BatchReq *__restr
 
 __global__ void k_batch_reset(int *head) { *head = 0; }
 
-// scaled a_lm of every synthesis request of a batch: grid.y = request (of
-// the list), grid.x = m.
+// c-scaled a_lm of every synthesis request of a batch: grid.y = request (of
+// the list), grid.x strides over its a_lm.
 __global__ __launch_bounds__(kBlock) void k_prescale_batch(const BatchReq *__restrict__ reqs,
                                                             const int32_t *__restrict__ list) {
     const BatchReq &R = reqs[list[blockIdx.y]];
-    const int m = blockIdx.x, lmax = R.syn.lmax;
-    if (m > R.syn.mmax) return;
-    const int64_t base = (int64_t)m * (2 * lmax + 1 - m) / 2;
-    prescale_column(lmax, m, R.alm_in + base, R.ana.fac, const_cast<double2 *>(R.syn.ap) + base);
+    const int64_t nalm = R.syn.nalm;
+    const int lmax = R.syn.lmax;
+    const double *__restrict__ cfac = R.ana.cfac;
+    double2 *out = const_cast<double2 *>(R.syn.ap);
+    for (int64_t k = blockIdx.x * (int64_t)kBlock + threadIdx.x; k < nalm; k += (int64_t)gridDim.x * kBlock) {
+        const double c = cfac[k];
+        const double2 a = R.alm_in[k];
+        out[k] = make_double2(a.x * c, k <= lmax ? 0.0 : a.y * c);  // Im a_l0 is ignored
+    }
 }
 
-// a_lm from the group sums (groups in order) for every analysis request of
-// the list that has several groups.
+// a_lm = c_lm * sum of the group partials (groups in order) for every
+// analysis request of the list that has several groups.
 __global__ __launch_bounds__(kBlock) void k_combine_batch(const BatchReq *__restrict__ reqs,
                                                            const int32_t *__restrict__ list) {
     const BatchReq &R = reqs[list[blockIdx.y]];
-    const int m = blockIdx.x, lmax = R.ana.lmax;
-    if (m > R.ana.mmax) return;
-    const int64_t nalm = R.ana.nalm, base = (int64_t)m * (2 * lmax + 1 - m) / 2;
-    finish_column(lmax, m, R.ana.fac, [&](int l) { return group_sum(R.ana.part, nalm, R.groups, base + l); },
-                  R.ana.alm + base);
+    const int64_t nalm = R.ana.nalm;
+    for (int64_t k = blockIdx.x * (int64_t)kBlock + threadIdx.x; k < nalm; k += (int64_t)gridDim.x * kBlock) {
+        const double2 v = group_sum(R.ana.part, nalm, R.groups, k);
+        const double c = R.ana.cfac[k];
+        R.ana.alm[k] = make_double2(v.x * c, k <= R.ana.lmax ? 0.0 : v.y * c);
+    }
 }
 
 }  // namespace
@@ -952,18 +853,18 @@ int launch_leg_batch(const BatchReq *reqs, const BatchItem *items, int nitems, i
     return SHT_OK;
 }
 
-int launch_prescale_batch(const BatchReq *reqs, const int32_t *syn_reqs, int nsyn, int max_m, hipStream_t st) {
+int launch_prescale_batch(const BatchReq *reqs, const int32_t *syn_reqs, int nsyn, int max_chunks, hipStream_t st) {
     if (nsyn <= 0) return SHT_OK;
     if (nsyn > 65535) return SHT_EUNSUPPORTED;
-    hipLaunchKernelGGL(k_prescale_batch, dim3((unsigned)max_m, (unsigned)nsyn), dim3(kBlock), 0, st, reqs, syn_reqs);
+    hipLaunchKernelGGL(k_prescale_batch, dim3((unsigned)max_chunks, (unsigned)nsyn), dim3(kBlock), 0, st, reqs, syn_reqs);
     SHT_HIP(hipGetLastError());
     return SHT_OK;
 }
 
-int launch_combine_batch(const BatchReq *reqs, const int32_t *comb_reqs, int ncomb, int max_m, hipStream_t st) {
+int launch_combine_batch(const BatchReq *reqs, const int32_t *comb_reqs, int ncomb, int max_chunks, hipStream_t st) {
     if (ncomb <= 0) return SHT_OK;
     if (ncomb > 65535) return SHT_EUNSUPPORTED;
-    hipLaunchKernelGGL(k_combine_batch, dim3((unsigned)max_m, (unsigned)ncomb), dim3(kBlock), 0, st, reqs, comb_reqs);
+    hipLaunchKernelGGL(k_combine_batch, dim3((unsigned)max_chunks, (unsigned)ncomb), dim3(kBlock), 0, st, reqs, comb_reqs);
     SHT_HIP(hipGetLastError());
     return SHT_OK;
 }
@@ -972,15 +873,16 @@ int launch_leg_start(const CoefTables &c, const GeomPlan &p, int32_t *jstart, vo
     const int tiles = (p.nslots + kBlock - 1) / kBlock;
     if (c.mmax + 1 > 65535) return SHT_EUNSUPPORTED;
     hipLaunchKernelGGL(k_leg_start, dim3((unsigned)tiles, (unsigned)(c.mmax + 1)), dim3(kBlock), 0, st, c.lmax,
-                       p.nslots, p.npolar, c.ra, c.rb, c.rbp, c.seed, p.slot_w, p.slot_s, jstart, static_cast<double2 *>(state));
+                       p.nslots, p.npolar, c.alpha, c.mu, p.slot_w, p.slot_s, jstart, static_cast<double2 *>(state));
     SHT_HIP(hipGetLastError());
     return SHT_OK;
 }
 
 int launch_prescale(const CoefTables &c, const void *alm, void *aprime, int nmaps, hipStream_t st) {
-    if (nmaps > 65535) return SHT_EUNSUPPORTED;
-    hipLaunchKernelGGL(k_prescale, dim3((unsigned)(c.mmax + 1), (unsigned)nmaps), dim3(kBlock), 0, st, c.nalm, c.lmax,
-                       static_cast<const double2 *>(alm), parity_fac(c), static_cast<double2 *>(aprime));
+    const int64_t total = c.nalm * nmaps;
+    const int64_t blocks = std::min<int64_t>((total + kBlock - 1) / kBlock, 1 << 16);
+    hipLaunchKernelGGL(k_prescale, dim3((unsigned)blocks), dim3(kBlock), 0, st, c.nalm, c.lmax, nmaps,
+                       static_cast<const double2 *>(alm), c.cfac, static_cast<double2 *>(aprime));
     SHT_HIP(hipGetLastError());
     return SHT_OK;
 }
@@ -1006,7 +908,6 @@ int launch_leg_syn(const CoefTables &c, const GeomPlan &p, const StartTable &s, 
     // slots a tile of kSynSlotsPerLane per lane would leave lanes and waves of
     // the workgroup idle while the others walk the recurrences of their slots
     // in turn; small transforms are bound by that sequential walk of the longest m.
-    // (Powers of two only: a wave's slots must not straddle GeomPlan::npolar.)
     const int T = p.nslots <= kBlock ? 1 : p.nslots <= (nmaps >= 2 ? 2 : 3) * kBlock ? 2 : kSynSlotsPerLane;
     // several maps share each recurrence: 2 maps per workgroup (at 4 slots per
     // lane faster than 4 maps and 2 slots: with the one-step recurrence 29.7 against 30.6 ms for 64 maps at
@@ -1073,13 +974,7 @@ int launch_leg_ana(const CoefTables &c, const GeomPlan &p, const StartTable &s, 
         }
     }
     SHT_HIP(hipGetLastError());
-    if (groups > 1) {
-        hipLaunchKernelGGL(k_ana_finish, dim3((unsigned)(c.mmax + 1), (unsigned)nmaps), dim3(kBlock), 0, st, c.nalm,
-                           c.lmax, groups, static_cast<const double2 *>(partials), parity_fac(c),
-                           static_cast<double2 *>(alm));
-        SHT_HIP(hipGetLastError());
-    }
-    return SHT_OK;
+    return groups > 1 ? launch_ana_combine(c, nmaps, groups, partials, alm, st) : SHT_OK;
 }
 
 int launch_ana_combine(const CoefTables &c, int nmaps, int groups, const void *partials, void *alm,

@@ -128,50 +128,20 @@ __global__ __launch_bounds__(kBlock) void k_prescale_mx(int lmax, int nmaps, int
     }
 }
 
-// Start of the one-step recurrence q_l (lambda_lm = c_lm q_l) of a slot, from
-// its tabulated start of the x^2 recurrence at l0 = m + 2 j0: with k = j0 - 1,
-// lambda_{l0-1} = x po_k q_k and lambda_{l0-2} = pe1_k q_k + pe2_{k-1} q_{k-1}
-// give (q_{l0-2}, q_{l0-1}); at j0 = 0 (-lambda_mm, 0) makes the first step
-// yield the seed.  ls = l0, or a value above lmax where the slot is not started.
+// Start of the one-step recurrence q_l of a slot: the tabulated start of the
+// pair recurrence at l = m + 2j holds p_{j-1} = q_{l-2} and r_{j-1} = q_{l-1} / x.
+// ls = that l, or a value above lmax where the slot is not started.
 struct MxStart {
     int ls;
     double2 st;
 };
-// T slots of a lane: one round of loads, and a second where the wave has a
-// start above l = m (no branch between the slots, so that they share it).
-template <int T>
-__device__ __forceinline__ void mx_starts(int lmax, int m, int nslots, const int (&slot)[T], const double (&x)[T],
-                                          ParityFac f, const double *__restrict__ cfac,
-                                          const int32_t *__restrict__ jstart, const double2 *__restrict__ state,
-                                          MxStart (&r)[T]) {
-    const int nj = jcol_len(lmax, m);
-    const int64_t jc = jcol_base(lmax, m), base = (int64_t)m * (2 * lmax + 1 - m) / 2;
-    int j0[T];
-    double2 s[T];
-    const double p0 = f.pe1[jc];
-    bool later = false;
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-        const int64_t at = (int64_t)m * nslots + min(slot[t], nslots - 1);
-        j0[t] = jstart[at];
-        s[t] = state[at];
-    }
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-        const bool starts = slot[t] < nslots && j0[t] < nj;
-        r[t].ls = starts ? m + 2 * j0[t] : lmax + 1;
-        r[t].st = make_double2(starts ? p0 * s[t].x : 0.0, 0.0);
-        if (starts && j0[t] > 0) later = true;
-    }
-    if (!__ballot(later)) return;
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-        const int k = max(min(j0[t], nj) - 1, 0), l = min(m + 2 * k + 1, lmax);
-        const double po = f.po[jc + k], pe1 = f.pe1[jc + k], pe2 = f.pe2[jc + max(k - 1, 0)];
-        const double c1 = cfac[base + l], c2 = cfac[base + m + 2 * k];
-        if (r[t].ls <= lmax && j0[t] > 0)
-            r[t].st = make_double2(fma(pe1, s[t].y, pe2 * s[t].x) / c2, x[t] * po * s[t].y / c1);
-    }
+__device__ __forceinline__ MxStart mx_start(int lmax, int m, int nslots, int slot, double x,
+                                            const int32_t *__restrict__ jstart, const double2 *__restrict__ state) {
+    const int64_t at = (int64_t)m * nslots + min(slot, nslots - 1);
+    const int j = jstart[at];
+    const double2 s = state[at];
+    const bool starts = slot < nslots && j < jcol_len(lmax, m);
+    return {starts ? m + 2 * j : lmax + 1, starts ? make_double2(s.x, x * s.y) : make_double2(0.0, 0.0)};
 }
 
 // LDS q tiles of one workgroup: per wave, parity and lane row, the four
@@ -190,8 +160,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_leg_syn_mx(int lmax, int mmax, in
                                                         int nmaps, int64_t mxblocks,
                                                         const int64_t *__restrict__ mxofs,
                                                         const void *__restrict__ ap,
-                                                        const double *__restrict__ alpha, ParityFac fac,
-                                                        const double *__restrict__ cfac,
+                                                        const double *__restrict__ alpha,
                                                         const int32_t *__restrict__ jstart,
                                                         const double2 *__restrict__ state,
                                                         const double *__restrict__ sx,
@@ -214,10 +183,9 @@ __global__ __launch_bounds__(kBlock, 2) void k_leg_syn_mx(int lmax, int mmax, in
     const int slot = tile * kBlock + (int)threadIdx.x;
     const bool act = slot < nslots;
     const double x = act ? sx[slot] : 0.0;
-    MxStart start[1];
-    mx_starts<1>(lmax, m, nslots, {slot}, {x}, fac, cfac, jstart, state, start);
-    const int ls = start[0].ls;
-    const double2 stv = start[0].st;
+    const MxStart start = mx_start(lmax, m, nslots, slot, x, jstart, state);
+    const int ls = start.ls;
+    const double2 stv = start.st;
     const int lo = wave_min(ls);
     const int hi = wave_max(ls <= lmax ? ls : m);
 
@@ -454,7 +422,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void k_leg_ana_mx(i
                                                               int nmaps, int64_t nalm, int groups,
                                                               const double2 *__restrict__ delta,
                                                               const double *__restrict__ alpha,
-                                                              const double *__restrict__ cfac, ParityFac fac,
+                                                              const double *__restrict__ cfac,
                                                               const int32_t *__restrict__ jstart,
                                                               const double2 *__restrict__ state,
                                                               const double *__restrict__ sx,
@@ -488,18 +456,14 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? 1 : 2) void k_leg_ana_mx(i
     float dp[kAnaMxTiles][16], dm[kAnaMxTiles][16];
     const double *__restrict__ dcol = reinterpret_cast<const double *>(delta) +
                                       2 * ((col_ok ? map_c : 0) * dl.s_map + m * dl.s_m) + (c16 & 1);
-    int mylo = lmax + 1, slot_of[kAnaMxTiles];
-    MxStart start[kAnaMxTiles];
+    int mylo = lmax + 1;
 #pragma unroll
     for (int t = 0; t < kAnaMxTiles; ++t) {
-        slot_of[t] = tile0(t) + lane;
-        x[t] = sx[min(slot_of[t], nslots - 1)];
-    }
-    mx_starts<kAnaMxTiles>(lmax, m, nslots, slot_of, x, fac, cfac, jstart, state, start);
-#pragma unroll
-    for (int t = 0; t < kAnaMxTiles; ++t) {
-        ls[t] = start[t].ls;
-        stv[t] = start[t].st;
+        const int slot = tile0(t) + lane;
+        x[t] = sx[min(slot, nslots - 1)];
+        const MxStart start = mx_start(lmax, m, nslots, slot, x[t], jstart, state);
+        ls[t] = start.ls;
+        stv[t] = start.st;
         q1[t] = q2[t] = 0.0;
     }
 #pragma unroll
@@ -664,7 +628,7 @@ int launch_syn_mx_t(const CoefTables &c, const GeomPlan &p, const StartTable &s,
     SHT_HIP(hipGetLastError());
     hipLaunchKernelGGL((k_leg_syn_mx<NCF, F64S, SPLIT>), dim3((unsigned)gx, (unsigned)ncg), dim3(kBlock), 0, st, c.lmax, c.mmax,
                        p.nslots, tiles, dl, nmaps, c.mxblocks, c.mxofs, static_cast<const void *>(aprime),
-                       c.alpha, parity_fac(c), c.cfac, s.jstart, s.state, p.slot_x, p.slot_north, p.slot_south,
+                       c.alpha, s.jstart, s.state, p.slot_x, p.slot_north, p.slot_south,
                        static_cast<double2 *>(delta));
     SHT_HIP(hipGetLastError());
     return SHT_OK;
@@ -681,7 +645,7 @@ int launch_ana_mx_t(const CoefTables &c, const GeomPlan &p, const StartTable &s,
     if (groups > 1 && !partials) return SHT_EWORKSPACE;
     hipLaunchKernelGGL(k_leg_ana_mx<WAVES>, dim3((unsigned)gx, (unsigned)ncg), dim3(64 * WAVES), 0, st, c.lmax,
                        c.mmax, p.nslots, dl, nmaps, c.nalm, groups, static_cast<const double2 *>(delta), c.alpha,
-                       c.cfac, parity_fac(c), s.jstart, s.state, p.slot_x, p.slot_north, p.slot_south, static_cast<double2 *>(alm),
+                       c.cfac, s.jstart, s.state, p.slot_x, p.slot_north, p.slot_south, static_cast<double2 *>(alm),
                        static_cast<double2 *>(partials));
     SHT_HIP(hipGetLastError());
     return groups > 1 ? launch_ana_combine(c, nmaps, groups, partials, alm, st) : SHT_OK;

@@ -130,7 +130,7 @@ struct sht_batch {
     BatchItem *items = nullptr;
     int32_t *syn_list = nullptr, *comb_list = nullptr;
     int nitems = 0, nsyn = 0, ncomb = 0, grid = 1;
-    int max_m = 1;
+    int syn_chunks = 1, comb_chunks = 1;
     int *head = nullptr;
     char *ws = nullptr;
     // ring stages of all requests: one launch per length class and direction
@@ -196,7 +196,7 @@ int sht_batch_create(int nreq, const sht_request *reqs, void *workspace, size_t 
     };
     std::vector<Work> work;
     std::vector<int32_t> syn_list, comb_list;
-    int max_mmax = 0;
+    int64_t max_nalm = 1;
     for (size_t i = 0; i < b->q.size(); ++i) {
         ReqPlan &q = b->q[i];
         const sht_request &r = q.r;
@@ -213,7 +213,7 @@ int sht_batch_create(int nreq, const sht_request *reqs, void *workspace, size_t 
         d.syn = syn_args(c, p, s, aux, delta);
         d.ana = ana_args(c, p, s, delta, r.out, aux);
         d.alm_in = static_cast<const double2 *>(r.in);
-        max_mmax = std::max(max_mmax, r.mmax);
+        max_nalm = std::max<int64_t>(max_nalm, c.nalm);
         const int lmax = r.lmax;
         // the cost of a unit: slot-recurrence steps of its busiest wave
         auto steps = [&](int m) { return (double)(lmax - m + 1); };
@@ -249,7 +249,7 @@ int sht_batch_create(int nreq, const sht_request *reqs, void *workspace, size_t 
     b->nitems = (int)items.size();
     b->nsyn = (int)syn_list.size();
     b->ncomb = (int)comb_list.size();
-    b->max_m = max_mmax + 1;
+    b->syn_chunks = b->comb_chunks = (int)std::min<int64_t>(4096, (max_nalm + kBlock - 1) / kBlock);
     if ((rc = upload_vec(b.get(), R, &b->reqs)) || (rc = upload_vec(b.get(), items, &b->items)) ||
         (rc = upload_vec(b.get(), syn_list, &b->syn_list)) || (rc = upload_vec(b.get(), comb_list, &b->comb_list)) ||
         (rc = leg_batch_grid(&b->grid)))
@@ -310,9 +310,9 @@ int sht_batch_run(sht_batch *b, void *stream) {
     // the alm2map requests; each ring stage one launch per length class over
     // the jobs of every request
     if ((rc = launch_fft_ana_batch(b->ring_ana, st)) ||
-        (rc = launch_prescale_batch(b->reqs, b->syn_list, b->nsyn, b->max_m, st)) ||
+        (rc = launch_prescale_batch(b->reqs, b->syn_list, b->nsyn, b->syn_chunks, st)) ||
         (rc = launch_leg_batch(b->reqs, b->items, b->nitems, b->head, b->grid, st)) ||
-        (rc = launch_combine_batch(b->reqs, b->comb_list, b->ncomb, b->max_m, st)) ||
+        (rc = launch_combine_batch(b->reqs, b->comb_list, b->ncomb, b->comb_chunks, st)) ||
         (rc = launch_fft_syn_batch(b->ring_syn, st)))
         return rc;
     return SHT_OK;

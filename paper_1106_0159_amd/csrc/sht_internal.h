@@ -54,22 +54,15 @@ constexpr int kScaleBits = 600;
 constexpr int kStartStep = 8;
 constexpr int kStartJ = kStartStep / 2;
 constexpr int kNeverJ = 1 << 29;  // start of a slot that is never started
-constexpr int kPolarSlots = 256;  // see GeomPlan::npolar
+constexpr int kMaxPolar = 256;  // see GeomPlan::npolar
 
-// Entries after the last column of alpha and of the x^2 recurrence's
-// coefficients (zeros) and of the scaled a_lm in the workspace: kernels read
-// blocks of coefficients up to 3 kStartStep - 1 entries (l) or 3 kStartJ - 1
-// (j) past the end of a column without a guard.
+// Entries after the last column of alpha (zeros) and of the c-scaled a_lm in
+// the workspace: kernels read blocks of coefficients past the end of a column
+// without a guard, 8 entries (kStartStep) at a time and up to two blocks ahead.
 constexpr int kCoefPad = 32;
 
-// The x^2 recurrence of column m has a value for each j with l = m + 2 j <=
-// lmax; its coefficients are packed by m, column m starting at jcol_base.
+// Number of pairs of degrees (m + 2j, m + 2j + 1) with m + 2j <= lmax.
 __host__ __device__ inline int jcol_len(int lmax, int m) { return (lmax - m) / 2 + 1; }
-__host__ __device__ inline int64_t jcol_base(int lmax, int m) {
-    // sum over m' < m of jcol_len = F(lmax) - F(lmax - m), F(n) = floor((n+2)^2 / 4)
-    const int64_t a = (int64_t)lmax + 2, b = a - m;
-    return a * a / 4 - b * b / 4;
-}
 
 // Mixed-precision Legendre stage: l runs in blocks of kMxL values counted
 // from m (kMxL / 2 of each parity of l - m); column m has mx_blocks(lmax, m).
@@ -95,22 +88,14 @@ struct Fenced {
 };
 
 // Coefficient tables for one (lmax, mmax) on one device.
-// Mixed-precision kernels, packed (l, m) index as for a_lm: lambda_lm =
-// cfac_lm q_lm, q_lm = alpha_lm x q_{l-1,m} - q_{l-2,m}.
-// FP64 kernels and start tables, packed by jcol_base: lambda_{m+2j+1,m} =
-// x r_j, r_j = C_j q_j, q_j = (A_j x^2 + B_j) q_{j-1} - q_{j-2}, and
-// lambda_{m+2j,m} = pe1_j q_j + pe2_{j-1} q_{j-1}, lambda_{m+2j+1,m} = po_j x q_j.
+// Packed (l, m) index as for a_lm.  lambda_lm = cfac_lm * q_lm, q_lm = alpha_lm x q_{l-1,m} - q_{l-2,m}.
 struct CoefTables : Fenced {
     int dev = -1;             // device holding the tables
     int lmax = -1, mmax = -1;
     int64_t nalm = 0;
     double *alpha = nullptr;  // [nalm + kCoefPad]; alpha at l = m is 0, at l = m+1 sqrt(2m+3)
     double *cfac = nullptr;   // [nalm]
-    // A_j, B_j and (polar slots) A_j + B_j, each [nj + kCoefPad] with nj =
-    // jcol_base(lmax, mmax + 1); 0 at j = 0
-    double *ra = nullptr, *rb = nullptr, *rbp = nullptr;
-    double *pe1 = nullptr, *pe2 = nullptr, *po = nullptr;  // [nj]
-    double *seed = nullptr;   // [mmax+1] mu_m sqrt(2m+3): q_0 = seed_m (-1)^m sin^m(theta)
+    double *mu = nullptr;     // [mmax+1]
     int64_t *mxofs = nullptr; // [mmax+2] first l-block of column m, blocks counted over m
     int64_t mxblocks = 0;     // sum over m of mx_blocks(lmax, m)
     std::vector<void *> owned;
@@ -139,8 +124,8 @@ struct FftDesc {
 
 // Where each (m, slot) recurrence starts, for one coefficient set on one
 // geometry plan: jstart[m * nslots + slot] is the first j of the block of
-// kStartJ steps in which |q_j| first reaches 2^-100 (kNeverJ if it never
-// does) and state[m * nslots + slot] = (q_{j-2}, q_{j-1}) before that step.
+// kStartJ steps in which |p_j| or |r_j| (k_legendre.hip) first reaches 2^-100
+// (kNeverJ if neither does) and state[m * nslots + slot] = (p_{j-1}, r_{j-1}).
 // A table built for (lmax', mmax') serves every lmax <= lmax', mmax <= mmax'.
 struct StartTable : Fenced {
     int dev = -1;
@@ -165,13 +150,12 @@ struct GeomPlan : Fenced {
     int all_nphi_max = 1;
     // slots: ring pairs (north, south) sharing one recurrence, sorted by sin(theta)
     double *slot_x = nullptr;        // cos(theta)
-    // Argument of the x^2 recurrence: the factor A x^2 + B of slot k is
-    // ra w + rb with w = x^2, or for the first npolar slots ra w + rbp with
-    // w = -(1 - x^2): next to a pole x^2 rounded to a double would move the
-    // ring by more than its distance from the pole allows.  npolar is
-    // kPolarSlots, or 0 for grids with fewer slots than that above 45 degrees
-    // (not as close to the poles): a multiple of every wave's 64 T slots, T =
-    // 1, 2, 4, so that a wave's slots are of one kind.
+    // x^2 as the recurrence takes it: slot_w itself, or for the first npolar
+    // slots 1 + slot_w, slot_w = -sin^2(theta): next to a pole x^2 rounded to a
+    // double would move the ring by more than its distance from the pole
+    // allows.  These are the slots with sin^2 < 1/2 (at 45 degrees both forms are
+    // equally good), at most kMaxPolar of them: the analysis kernels look for
+    // them in their first sets of slots only.
     double *slot_w = nullptr;
     int npolar = 0;
     double2 *slot_s = nullptr;       // sin(theta) as an unevaluated sum of two doubles
@@ -308,15 +292,13 @@ void set_hip_error(hipError_t e, const char *where);
     } while (0)
 
 // Arguments of the FP64 Legendre tiles (k_legendre.hip) for one (lmax, mmax,
-// geometry): synthesis reads the scaled a_lm (ap) and writes ring-major
+// geometry): synthesis reads the c-scaled a_lm (ap) and writes ring-major
 // Delta; analysis reads Delta and writes a_lm (or per-group partials).
 struct SynArgs {
     int lmax, mmax, nslots, nrings, npolar;
     int64_t nalm;
     const double2 *__restrict__ ap;
-    const double *__restrict__ ra;
-    const double *__restrict__ rb;
-    const double *__restrict__ rbp;
+    const double *__restrict__ alpha;
     const int32_t *__restrict__ jstart;
     const double2 *__restrict__ state;
     const double *__restrict__ sx;
@@ -326,22 +308,12 @@ struct SynArgs {
     double2 *__restrict__ delta;
 };
 
-// Factors that turn the sums over q_j into a_lm (and a_lm into the scaled
-// coefficients of the synthesis); see CoefTables.
-struct ParityFac {
-    const double *__restrict__ pe1;
-    const double *__restrict__ pe2;
-    const double *__restrict__ po;
-};
-
 struct AnaArgs {
     int lmax, mmax, nslots, nrings, npolar;
     int64_t nalm;
     const double2 *__restrict__ delta;
-    const double *__restrict__ ra;
-    const double *__restrict__ rb;
-    const double *__restrict__ rbp;
-    ParityFac fac;
+    const double *__restrict__ alpha;
+    const double *__restrict__ cfac;
     const int32_t *__restrict__ jstart;
     const double2 *__restrict__ state;
     const double *__restrict__ sx;
@@ -352,14 +324,13 @@ struct AnaArgs {
     double2 *__restrict__ part;
 };
 inline SynArgs syn_args(const CoefTables &c, const GeomPlan &p, const StartTable &s, const void *ap, void *delta) {
-    return SynArgs{c.lmax, c.mmax, p.nslots, p.nrings, p.npolar, c.nalm, static_cast<const double2 *>(ap), c.ra,
-                   c.rb, c.rbp, s.jstart, s.state, p.slot_x, p.slot_w, p.slot_north, p.slot_south, static_cast<double2 *>(delta)};
+    return SynArgs{c.lmax, c.mmax, p.nslots, p.nrings, p.npolar, c.nalm, static_cast<const double2 *>(ap), c.alpha,
+                   s.jstart, s.state, p.slot_x, p.slot_w, p.slot_north, p.slot_south, static_cast<double2 *>(delta)};
 }
-inline ParityFac parity_fac(const CoefTables &c) { return ParityFac{c.pe1, c.pe2, c.po}; }
 inline AnaArgs ana_args(const CoefTables &c, const GeomPlan &p, const StartTable &s, const void *delta, void *alm,
                         void *part) {
-    return AnaArgs{c.lmax, c.mmax, p.nslots, p.nrings, p.npolar, c.nalm, static_cast<const double2 *>(delta), c.ra,
-                   c.rb, c.rbp, parity_fac(c), s.jstart, s.state, p.slot_x, p.slot_w, p.slot_north, p.slot_south,
+    return AnaArgs{c.lmax, c.mmax, p.nslots, p.nrings, p.npolar, c.nalm, static_cast<const double2 *>(delta), c.alpha,
+                   c.cfac, s.jstart, s.state, p.slot_x, p.slot_w, p.slot_north, p.slot_south,
                    static_cast<double2 *>(alm), static_cast<double2 *>(part)};
 }
 
@@ -402,11 +373,11 @@ int launch_leg_ana_mx(const CoefTables &c, const GeomPlan &p, const StartTable &
 // kernel on the current device.
 int leg_batch_grid(int *grid);
 int launch_leg_batch(const BatchReq *reqs, const BatchItem *items, int nitems, int *head, int grid, hipStream_t st);
-int launch_prescale_batch(const BatchReq *reqs, const int32_t *syn_reqs, int nsyn, int max_m, hipStream_t st);
-int launch_combine_batch(const BatchReq *reqs, const int32_t *comb_reqs, int ncomb, int max_m, hipStream_t st);
+int launch_prescale_batch(const BatchReq *reqs, const int32_t *syn_reqs, int nsyn, int max_chunks, hipStream_t st);
+int launch_combine_batch(const BatchReq *reqs, const int32_t *comb_reqs, int ncomb, int max_chunks, hipStream_t st);
 constexpr int kBatchMaxSynT = 4, kBatchMaxAnaT = 4;
 
-// Mixed analysis: a_lm = c_lm * (sum of the per-group partials, groups in order); Im a_l0 = 0.
+// a_lm = c_lm * (sum of the per-group partials, groups in order); Im a_l0 = 0.
 int launch_ana_combine(const CoefTables &c, int nmaps, int groups, const void *partials, void *alm,
                        hipStream_t st);
 // Ring stages: the length classes run concurrently on side streams of st

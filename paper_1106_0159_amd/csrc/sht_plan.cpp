@@ -222,71 +222,19 @@ GeomPlan::~GeomPlan() {
 // For one m: beta_l = sqrt((4l^2-1)/(l^2-m^2)) (eq. betaDef), c_m = c_{m+1} = 1,
 // c_l = (beta_l/beta_{l-1}) c_{l-2}, alpha_l = beta_l c_{l-1}/c_l.  Then
 // p_l = c_l q_l turns eq. assLegRec into q_l = alpha_l x q_{l-1} - q_{l-2}.
-// alpha is derived from the stored (rounded) c so that the effective
-// recurrence coefficients carry only their own rounding.
+// c is carried in long double: its rounding stays out of the recurrence.
 static void coef_column(int lmax, int m, double *alpha, double *cfac) {
-    const int n = lmax - m + 1;
-    std::vector<long double> beta(n + 1, 0.0L);
-    for (int l = m + 1; l <= lmax; ++l) {
-        const long double L = l, M = m;
-        beta[l - m] = sqrtl((4.0L * L * L - 1.0L) / (L * L - M * M));
-    }
+    long double b0 = 0.0L, c0 = 1.0L, c1 = 1.0L;  // beta_{l-1}, c_{l-2}, c_{l-1}
     cfac[0] = 1.0;
     alpha[0] = 0.0;
-    if (lmax >= m + 1) {
-        cfac[1] = 1.0;
-        alpha[1] = (double)beta[1];  // sqrt(2m+3), eq. pm1m
-    }
-    for (int l = m + 2; l <= lmax; ++l) {
-        const int i = l - m;
-        const long double c = beta[i] / beta[i - 1] * (long double)cfac[i - 2];
-        cfac[i] = (double)c;
-        alpha[i] = (double)(beta[i] * (long double)cfac[i - 1] / (long double)cfac[i]);
-    }
-}
-
-// The x^2 recurrence of one m (FP64 kernels).  eq. assLegRec, lambda_l =
-// beta_l x lambda_{l-1} - rho_l lambda_{l-2} with rho_l = beta_l / beta_{l-1},
-// applied twice steps by two in l; for r_j = lambda_k / x, k = m + 2j + 1,
-//   r_{j+1} = (beta_{k+2} beta_{k+1} x^2 - beta_{k+2} rho_{k+1} / beta_k - rho_{k+2}) r_j
-//             - (beta_{k+2} rho_{k+1} rho_k / beta_k) r_{j-1},
-// and the even degrees are lambda_{k-1} = (r_j + rho_k r_{j-1}) / beta_k.  With
-// r_j = C_j q_j, C_0 = C_1 = 1 and C_{j+1} = (the factor of r_{j-1}) C_{j-1},
-// the coefficient of q_{j-1} is -1; C_j is carried in long double, so that its
-// rounding stays out of the recurrence.
-//
-// rbp = A_j + B_j goes with the argument x^2 - 1 of the slots next to the poles
-// (GeomPlan::npolar).  All are formed in long double and rounded once.
-static void x2_column(int lmax, int m, double *ra, double *rb, double *rbp, double *pe1, double *pe2, double *po) {
-    const int n = jcol_len(lmax, m);
-    ra[0] = rb[0] = rbp[0] = 0.0;
-    {
-        auto beta = [m](int l) {
-            const long double L = l, M = m;
-            return sqrtl((4.0L * L * L - 1.0L) / (L * L - M * M));
-        };
-        // with rho = beta / beta' the factors reduce to h_j = 1 / (beta_{k+1}
-        // beta_{k+2}): A_j = C_{j-1} / (C_j h), factor of r_{j-1} = h_{j-1} / h_j
-        long double c0 = 1.0L, c1 = 1.0L, h0 = 0.0L, b0 = beta(m + 1);  // C_{j-1}, C_j, h_{j-1}, beta_k
-        for (int j = 0; j < n; ++j) {
-            const int k = m + 2 * j + 1;
-            const long double b1 = beta(k + 1), b2 = beta(k + 2), i0 = 1.0L / b0, i1 = 1.0L / b1;
-            pe1[j] = (double)(c1 * i0);
-            pe2[j] = (double)(c1 * i1);
-            po[j] = (double)c1;
-            const long double h = i1 / b2, hinv = b1 * b2;
-            const long double c2 = j == 0 ? 1.0L : h0 * hinv * c0;  // C_{j+1}
-            if (j + 1 < n) {
-                const long double a = c1 / c2 * hinv;
-                ra[j + 1] = (double)a;
-                rb[j + 1] = (double)(-a * (i0 * i0 + i1 * i1));
-                rbp[j + 1] = (double)(a * (1.0L - i0 * i0 - i1 * i1));
-            }
-            c0 = c1;
-            c1 = c2;
-            h0 = h;
-            b0 = b2;
-        }
+    for (int l = m + 1; l <= lmax; ++l) {
+        const long double L = l, M = m, b = sqrtl((4.0L * L * L - 1.0L) / (L * L - M * M));
+        const long double c = l == m + 1 ? 1.0L : b / b0 * c0;
+        cfac[l - m] = (double)c;
+        alpha[l - m] = (double)(b * c1 / c);  // sqrt(2m+3) at l = m+1, eq. pm1m
+        c0 = c1;
+        c1 = c;
+        b0 = b;
     }
 }
 
@@ -312,36 +260,27 @@ static int build_coef(int dev, int lmax, int mmax, std::shared_ptr<CoefTables> *
     auto t = std::make_shared<CoefTables>();
     t->dev = dev;
     const int64_t na = nalm_of(lmax, mmax);
-    std::vector<double> alpha(na), cfac(na), seed(mmax + 1);
-    const int64_t nj = jcol_base(lmax, mmax + 1);
-    std::vector<double> ra(nj), rb(nj), rbp(nj), pe1(nj), pe2(nj), po(nj);
+    std::vector<double> alpha(na), cfac(na), mu(mmax + 1);
     for (int m = 0; m <= mmax; ++m) {
         const int64_t b = (int64_t)m * (2 * (int64_t)lmax + 1 - m) / 2 + m;
         coef_column(lmax, m, alpha.data() + b, cfac.data() + b);
-        const int64_t jb = jcol_base(lmax, m);
-        x2_column(lmax, m, ra.data() + jb, rb.data() + jb, rbp.data() + jb, pe1.data() + jb, pe2.data() + jb, po.data() + jb);
     }
-    // mu_m of eq. pmm: mu_0 = 1/sqrt(4 pi), mu_m = mu_{m-1} sqrt((2m+1)/(2m));
-    // q_0 = r_0 = lambda_{m+1,m} / x = sqrt(2m+3) lambda_mm (eq. pm1m)
+    // mu_m of eq. pmm: mu_0 = 1/sqrt(4 pi), mu_m = mu_{m-1} sqrt((2m+1)/(2m))
     long double v = 1.0L / sqrtl(4.0L * 3.141592653589793238462643383279502884L);
     for (int m = 0; m <= mmax; ++m) {
         if (m > 0) v *= sqrtl((long double)(2 * m + 1) / (long double)(2 * m));
-        seed[m] = (double)(v * sqrtl((long double)(2 * m + 3)));
+        mu[m] = (double)v;
     }
     t->lmax = lmax;
     t->mmax = mmax;
     t->nalm = na;
     alpha.resize(na + kCoefPad, 0.0);  // kernels may read past the last column
-    for (auto *t2 : {&ra, &rb, &rbp}) t2->resize(nj + kCoefPad, 0.0);
     std::vector<int64_t> mxofs(mmax + 2, 0);
     for (int m = 0; m <= mmax; ++m) mxofs[m + 1] = mxofs[m] + mx_blocks(lmax, m);
     t->mxblocks = mxofs[mmax + 1];
     int rc;
     if ((rc = upload(alpha, &t->alpha, t->owned)) || (rc = upload(cfac, &t->cfac, t->owned)) ||
-        (rc = upload(ra, &t->ra, t->owned)) || (rc = upload(rb, &t->rb, t->owned)) || (rc = upload(rbp, &t->rbp, t->owned)) ||
-        (rc = upload(pe1, &t->pe1, t->owned)) ||
-        (rc = upload(pe2, &t->pe2, t->owned)) || (rc = upload(po, &t->po, t->owned)) ||
-        (rc = upload(seed, &t->seed, t->owned)) || (rc = upload(mxofs, &t->mxofs, t->owned)))
+        (rc = upload(mu, &t->mu, t->owned)) || (rc = upload(mxofs, &t->mxofs, t->owned)))
         return rc;  // t frees what was uploaded
     *out = std::move(t);
     return SHT_OK;
@@ -621,7 +560,7 @@ static bool same_geom(const HostGeom &a, const HostGeom &b) {
 // further off mirror is its own slot, evaluated at its own colatitude.
 constexpr long double kMirrorTol = 0x1p-50L;  // 2 ulp of pi = 8.9e-16 rad
 struct SlotTables {
-    std::vector<double> x, w;  // cos(theta), argument of the x^2 recurrence
+    std::vector<double> x, w;  // cos(theta), x^2 as the recurrence takes it (GeomPlan::slot_w)
     std::vector<double2> s;    // sin(theta) in two doubles
     std::vector<int32_t> north, south;
     int npolar = 0;
@@ -661,7 +600,7 @@ static SlotTables build_slots(const HostGeom &h) {
     SlotTables t;
     int near_pole = 0;
     for (const S &s : slots) near_pole += s.s * s.s < 0.5;
-    t.npolar = near_pole < kPolarSlots ? 0 : kPolarSlots;
+    t.npolar = std::min(near_pole, kMaxPolar);
     for (const S &s : slots) {
         const long double th = h.theta[s.n], sn = sinl(th);
         const double c = std::cos(h.theta[s.n]);
