@@ -972,6 +972,7 @@ __global__ __launch_bounds__(NT, 4) void k_fft_syn(RingPlan one, const RingPlan 
                 const int k = threadIdx.x + u * NT, kn = k ? N - k : 0;
                 if (2 * k <= N) {
                     double2 a = fa[u], b = fb[u];  // zero above mmax
+                    if (!k) a.y = b.y = 0.0;       // Im Delta_0 is ignored, whatever it is
                     if constexpr (TURN) {
                         const double2 e = pha(min(k, mmax));
                         a = cmul(a, e);
