@@ -31,7 +31,13 @@ if ROOT not in sys.path:
 PEAK_FP64_VALU_TFLOPS = 78.6   # 256 CU x 4 SIMD x 16 lanes x 2 flop (FMA) x 2.4 GHz
 PEAK_FP32_MFMA_TFLOPS = 157.3  # dense FP32 matrix-core peak
 PEAK_HBM_GBS = 8000.0
-FLOPS_PER_TRIPLE = 8           # recurrence 4 + complex-by-real contraction 4 per (slot, l, m)
+# FP64 flops of the Legendre kernels per (slot, l, m) and map: the recurrence (one
+# product and two fused multiply-adds for two degrees, so 2.5 a degree, shared by
+# the maps of a workgroup) and a complex-by-real contraction (4).  Counted over
+# all triples; the kernels skip those whose lambda_lm is negligible (a quarter).
+RECURRENCE_FLOPS, CONTRACTION_FLOPS = 2.5, 4.0
+FLOPS_PER_TRIPLE = RECURRENCE_FLOPS + CONTRACTION_FLOPS
+FLOPS_PER_TRIPLE_BATCH = {"leg_syn": RECURRENCE_FLOPS / 2 + CONTRACTION_FLOPS, "leg_ana": FLOPS_PER_TRIPLE}
 DOMINANT_SOURCES = ["paper_1106_0159_amd/csrc/k_legendre.hip", "paper_1106_0159_amd/csrc/k_device.h"]
 
 
@@ -208,6 +214,7 @@ def batch_record(nmaps, st, batch_ms, wall_ms, steps, dtype, flops_per_launch, p
     """Throughput, stage times and the roofline of the slower Legendre stage."""
     ms = max(wall_ms, sum(st.values()))
     dom = max(("leg_syn", "leg_ana"), key=lambda n: st[n])
+    flops_per_launch = flops_per_launch[dom]
     achieved = flops_per_launch / (st[dom] * 1e-3) / 1e12
     return {
         "nmaps": nmaps,
@@ -255,7 +262,15 @@ def power_law_batch(si, lmax, nmaps, config):
 
 
 MX_KERNELS = {"leg_syn": "k_prescale_mx + k_leg_syn_mx", "leg_ana": "k_leg_ana_mx"}
-F64_KERNELS = {"leg_syn": "k_prescale + k_leg_syn", "leg_ana": "k_leg_ana (+ k_ana_finish above 2048 slots)"}
+F64_KERNELS = {"leg_syn": "k_prescale + k_leg_syn_mm", "leg_ana": "k_leg_ana (+ k_ana_combine above 2048 slots)"}
+
+
+def mixed_flops(nmaps, triples):
+    return dict.fromkeys(("leg_syn", "leg_ana"), 4 * nmaps * triples)
+
+
+def fp64_flops(nmaps, triples):
+    return {stage: f * nmaps * triples for stage, f in FLOPS_PER_TRIPLE_BATCH.items()}
 
 
 def rel_per_map(x, y):
@@ -277,12 +292,12 @@ def batched_legs(sht, si, gh, g, lmax, nmaps, steps, warmup, nslots, mp_fp64, a_
     (SHT_MIXED alone, one FP32 l-chain) and of SHT_MIXED_FP64_SUMS (FP32
     products, synthesis block sums added in FP64)."""
     alm = power_law_batch(si, lmax, nmaps, 2)
-    flops_mx = 4 * nmaps * count_triples(nslots, lmax, lmax)
+    flops_mx = mixed_flops(nmaps, count_triples(nslots, lmax, lmax))
     fsp = sht.SHT_MIXED | sht.SHT_MIXED_SPLIT_BF16
     st, bm, wall, mp_x, a_x = run_batch(sht, gh, g, lmax, alm, steps, warmup, fsp)
     mx = batch_record(nmaps, st, bm, wall, steps, "f64 recurrence; synthesis 3 x bf16 split products, "
                       "analysis f32 products; f32 accumulation", flops_mx, PEAK_FP32_MFMA_TFLOPS, "mfma", MX_KERNELS)
-    flops_64 = FLOPS_PER_TRIPLE * nmaps * count_triples(nslots, lmax, lmax)
+    flops_64 = fp64_flops(nmaps, count_triples(nslots, lmax, lmax))
     st, bm, wall, mp_d, a_d = run_batch(sht, gh, g, lmax, alm, steps, warmup, 0)
     f64 = batch_record(nmaps, st, bm, wall, steps, "f64", flops_64, PEAK_FP64_VALU_TFLOPS, "alu", F64_KERNELS)
     rel = lambda x, y: (x - y).norm().item() / y.norm().item()
@@ -334,11 +349,11 @@ def config3(sht, si, steps, warmup, with_oracle):
     st, bm, wall, mp_x, a_x = run_batch(sht, gh, g, lmax, alm, steps, warmup,
                                         sht.SHT_MIXED | sht.SHT_MIXED_SPLIT_BF16)
     mx = batch_record(nmaps, st, bm, wall, steps, "f64 recurrence; synthesis 3 x bf16 split products, "
-                      "analysis f32 products; f32 accumulation", 4 * nmaps * tri, PEAK_FP32_MFMA_TFLOPS, "mfma",
+                      "analysis f32 products; f32 accumulation", mixed_flops(nmaps, tri), PEAK_FP32_MFMA_TFLOPS, "mfma",
                       MX_KERNELS)
     st, bm, wall, mp_d, a_d = run_batch(sht, gh, g, lmax, alm, steps, warmup, 0)
-    f64 = batch_record(nmaps, st, bm, wall, steps, "f64", FLOPS_PER_TRIPLE * nmaps * tri,
-                       PEAK_FP64_VALU_TFLOPS, "alu", F64_KERNELS)
+    f64 = batch_record(nmaps, st, bm, wall, steps, "f64", fp64_flops(nmaps, tri), PEAK_FP64_VALU_TFLOPS, "alu",
+                       F64_KERNELS)
     e_map = rel_per_map(mp_x, mp_d)
     e_rt_x, e_rt_d = rel_per_map(a_x, alm), rel_per_map(a_d, alm)
     out = {
@@ -712,7 +727,7 @@ def main():
         "map2alm_maps_per_s": 1000.0 / (stage_ms["fft_ana"] + stage_ms["leg_ana"]),
         "roofline": {
             "kernel": {"leg_syn": "k_prescale + k_leg_syn",
-                       "leg_ana": "k_leg_ana (+ k_ana_finish above 2048 slots)"}[dom],
+                       "leg_ana": "k_leg_ana (+ k_ana_combine above 2048 slots)"}[dom],
             "bound": "alu",
             "achieved": achieved,
             "peak": PEAK_FP64_VALU_TFLOPS,

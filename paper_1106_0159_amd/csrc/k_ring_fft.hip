@@ -858,7 +858,7 @@ inline int64_t fft_grid(int njobs, int nmaps, int map_minor) {
 // E_k = (Z_k + conj Z_{n-k}) / 2, O_k = (Z_k - conj Z_{n-k}) / (2i), k <= n.
 // The turns e^{i pi k / n} come from the chirp's own tables.
 // Fold of a synthesis job: the transform's input points conj(E + i O).
-template <int MAXL, int NT>
+template <int NT>
 __device__ __forceinline__ void half_fold(const double2 *__restrict__ D, int64_t sm, int mmax, int n, const Chirp &ch, const Phase &ph, double2 *buf) {
     const int N = 2 * n;
     auto herm = [&](double2 c0, double2 c1) { return make_double2(0.5 * (c0.x + c1.x), 0.5 * (c0.y - c1.y)); };
@@ -952,7 +952,7 @@ __global__ __launch_bounds__(NT, 4) void k_fft_syn(RingPlan one, const RingPlan 
     }
     if (P.ph_tab || blue) __syncthreads();  // phase and chirp tables visible
     if (half) {
-        half_fold<MAXL, NT>(Da, dl.s_m, mmax, N, ch, pha, buf);
+        half_fold<NT>(Da, dl.s_m, mmax, N, ch, pha, buf);
     } else if (plain) {
         // TURN: phi0 != 0; BOTH: n < 2 mmax, bins take m = n - k too
         auto fold = [&](auto turn, auto both) {

@@ -57,8 +57,10 @@ constexpr int kNeverJ = 1 << 29;  // start of a slot that is never started
 constexpr int kMaxPolar = 256;  // see GeomPlan::npolar
 
 // Entries after the last column of alpha (zeros) and of the c-scaled a_lm in
-// the workspace: kernels read blocks of coefficients past the end of a column
-// without a guard, 8 entries (kStartStep) at a time and up to two blocks ahead.
+// the workspace, which kernels read without a guard past lmax.  The farthest: of
+// alpha 31 entries by the mixed kernels (blocks of 32 degrees that hold lmax) and
+// 15 by the FP64 analysis (a chunk of 8 begun at lmax and the next), of a_lm 4 by
+// the synthesis (half a block of 8 ahead).
 constexpr int kCoefPad = 32;
 
 // Number of pairs of degrees (m + 2j, m + 2j + 1) with m + 2j <= lmax.
@@ -105,11 +107,12 @@ struct CoefTables : Fenced {
     ~CoefTables();            // waits for the streams that used it, then frees
 };
 
-// One FFT length (device view).  Points of length n are transformed in LDS
-// either directly (L == n, radices of n) or by Bluestein's chirp-z method
-// with the shortest 5-smooth length L >= 2n - 2.
 // second entry of the job of a ring transformed by itself (FftDesc::half); -1: no second ring
 constexpr int kHalfJob = -2;
+
+// One FFT length (device view).  Points of length n are transformed in LDS
+// either directly (L == n, radices of n) or by Bluestein's chirp-z method
+// with the shortest class length L >= 2n - 2.
 struct FftDesc {
     int n;                 // points of the transform (half the ring's when half)
     int L;

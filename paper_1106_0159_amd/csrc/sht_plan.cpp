@@ -363,12 +363,6 @@ static bool factor_all(int n, std::vector<int> &rad) {
 // pair on 4096 points 109 and 22 (n = 2036), the halves on 2048 117 and 18.
 constexpr double kBaseCost = 90.0, kPairCost = 118.0, kHalfCost = 200.0;
 
-static bool smooth5(int n) {
-    for (int p : {2, 3, 5})
-        while (n % p == 0) n /= p;
-    return n == 1;
-}
-
 // Forward DFT (sign -1) of a power-of-two length in long double, in place, w
 // the roots exp(-2 pi i t / L), t < L / 2: radix 2 on bit-reversed points.
 static void host_fft_pow2(std::vector<cld> &a, const std::vector<cld> &w) {
