@@ -952,15 +952,20 @@ int launch_leg_ana(const CoefTables &c, const GeomPlan &p, const StartTable &s, 
         // one wave holds every slot: no step across waves (lmax 64 on 64
         // slots: 10.2 us for the stage against 11.6 with a workgroup)
         hipLaunchKernelGGL(k_leg_ana_wave, dim3((unsigned)padded_m(c.mmax), (unsigned)nmaps), dim3(64), 0, st, A);
-    } else if (p.nslots > 512 && p.nslots <= 640) {
-        // Two waves of 5 slots per lane add half the wave sums of four waves of
-        // 3: 64 maps on 513 slots, lmax 1024, 3.51 against 4.69 ms for the
-        // stage, one map 115 against 107 us.  Up to 512 slots one map leaves
-        // the chip with too few waves for that, and from 641 on (6 per lane) it
-        // costs one map more than it gives several (694 slots, lmax 694: one
-        // map 82 and 68 us, eight 289 and 338).
-        static_assert(5 * 2 * 64 == 640, "one group");
-        launch_ana_t<5, 2>(A, groups, nmaps, st);
+    } else if (p.nslots <= 192 || (p.nslots > 512 && p.nslots <= 640)) {
+        // Two waves of up to 5 slots per lane instead of four: fewer wave sums, and
+        // no idle waves on up to 3 sets of 64 slots.  Stage for one and for 64 maps:
+        // 129 slots, lmax 256, 21.9 and 171 us (four waves 22.7 and 254); 513 slots,
+        // lmax 1024, 119 us and 3.36 ms (108 and 4.46).  On 193 to 512 slots one map
+        // leaves the chip with too few waves for that (226 slots, lmax 450, one and
+        // eight maps: 34.5 and 92 us, four waves 31.7 and 126), and from 641 on two
+        // waves of 6 and more cost one map more than they give several (694 slots,
+        // lmax 694: 90 and 293 us, four waves 73 and 333).
+        switch ((p.nslots + 127) / 128) {
+            case 1: launch_ana_t<1, 2>(A, groups, nmaps, st); break;
+            case 2: launch_ana_t<2, 2>(A, groups, nmaps, st); break;
+            default: launch_ana_t<5, 2>(A, groups, nmaps, st); break;
+        }
     } else {
         switch (T) {
             case 1: launch_ana_t<1>(A, groups, nmaps, st); break;

@@ -28,12 +28,11 @@ constexpr int kFftClassLen[kFftClasses] = {1024, 2048, 4096, 8192};
 constexpr int kAnaThreads = 256;
 constexpr int kAnaSlotsPerThread = 8;
 
-// Slots per lane: the fewest that put every slot in one workgroup, up to
-// kAnaSlotsPerThread.  Fewer waves of more slots each add up fewer wave sums,
-// but one map then leaves the chip with too few waves: four waves were the
-// fastest at every size from 129 to 2048 slots (513 slots, lmax 1024: 99 us
-// against 115 with two waves of 5 and 159 with one of 9; 2048 slots, lmax
-// 2048: 537 against 632 us with two groups of two waves).
+// Slots per lane of a workgroup of four waves: the fewest that put every slot in
+// one workgroup, up to kAnaSlotsPerThread.  Fewer waves of more slots each add up
+// fewer wave sums, but leave one map with too few waves for the chip (1024 slots,
+// lmax 1024: 135 us against 166 with two waves of 8; 694 slots, lmax 694: 73
+// and 90).  launch_leg_ana takes two waves where that pays all the same.
 inline int ana_slots_per_thread(int nslots) {
     const int t = (nslots + kAnaThreads - 1) / kAnaThreads;
     return t < kAnaSlotsPerThread ? t : kAnaSlotsPerThread;

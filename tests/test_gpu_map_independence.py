@@ -23,7 +23,8 @@ def rings(nslots, seed):
                     f"independent{nslots}")
 
 
-@pytest.mark.parametrize("nslots", [64, 65, 256, 257, 512, 513, 770, 1024, 1025, 1400, 2048, 2049, 2600])
+@pytest.mark.parametrize("nslots", [64, 65, 128, 129, 192, 193, 256, 257, 512, 513, 640, 641, 770, 1024, 1025, 1400, 2048,
+                                    2049, 2600])
 def test_maps_of_a_call_are_independent(nslots):
     import torch
     import paper_1106_0159_amd as sht
